@@ -7,11 +7,8 @@
 
 #include <type_traits>
 
+#include "split_mfma.hpp"
 #include "tile_mfma.hpp"
-
-#ifndef SHP_EPI_VEC
-#define SHP_EPI_VEC 1
-#endif
 
 namespace shp {
 
@@ -79,7 +76,6 @@ struct GemmProblem {
   int sym;        // symmetric output: compute tiles ti <= tj, mirror into the lower part
   int tiles_n;    // ceil(N / 128)
   int tile_begin; // first logical tile of this problem
-  int a_aligned, b_aligned;
   // Optional device-side limits (embedding rows, whose count is known only
   // on the device), honoured by the LIM instantiation:
   //   ksplit == 0: K is cut to *kcount - koff (>= 0);
@@ -130,17 +126,11 @@ __device__ __forceinline__ void epi_rows(const float* epi, float* dst, int64_t l
 // instantiation, so the plain kernels carry no extra registers).
 // SGG (not void): element type of G for the fused graft pass 1 (problems
 // with gD set; a separate instantiation as well).
-// WN = 2: 128 x 256 output tiles (plain outputs, both operands k-major;
-// tiles_n counts 256-wide tile columns).
 // map: how workgroups find their tiles (kMapXcd, kMapDeal, kMapDiagLast).
-template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void, int WN = 1>
+template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
 __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const GemmProblem* __restrict__ probs,
                                                                int nprob, int total_tiles, int map) {
-  static_assert(WN == 1 || (!LIM && LA == kLayoutK && LB == kLayoutK), "wide tiles: plain k-major products");
-  constexpr int TN = kTile * WN;  // output tile width
-  __shared__ __attribute__((aligned(16))) float sa0[StageElems<float, LA>::value], sa1[StageElems<float, LA>::value];
-  __shared__ __attribute__((aligned(16))) float sb0[StageElems<float, LB, TN>::value],
-      sb1[StageElems<float, LB, TN>::value];
+  __shared__ __attribute__((aligned(16))) char smem[SplitShm<SA, SB>::bytes];
   // LIM: work depends on device-side counts and sits in the first logical
   // tiles; dispatch order (round robin over the XCDs) spreads it evenly.
   int pi, ti, tj, lt = 0;  // lt: the tile's index in its problem (graft partial slots)
@@ -180,12 +170,13 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
       tj = lt % tn;
     }
   }
-  const GemmProblem P = probs[pi];
-  const int m0 = ti * kTile, n0 = tj * TN;
-  if (LIM && P.mcount && m0 >= *P.mcount) return;
+  GemmProblem P = probs[pi];
+  if (LIM && P.mcount) P.M = P.a_rows = min(P.M, *P.mcount);
+  const int m0 = ti * kTile, n0 = tj * kTile;
+  if (LIM && m0 >= P.M) return;
 
-  Operand<SA> A{reinterpret_cast<const SA*>(P.A), P.lda, P.a_rows, P.a_cols, P.a_aligned != 0};
-  Operand<SB> B{reinterpret_cast<const SB*>(P.B), P.ldb, P.b_rows, P.b_cols, P.b_aligned != 0};
+  Operand<SA> A{reinterpret_cast<const SA*>(P.A), P.lda, P.a_rows, P.a_cols};
+  Operand<SB> B{reinterpret_cast<const SB*>(P.B), P.ldb, P.b_rows, P.b_cols};
   int K = P.K;
   if (LIM && P.kcount) {
     const int cnt = *P.kcount;
@@ -206,9 +197,10 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
     if (LA == kLayoutK) A.rows = min(A.rows, K); else A.cols = min(A.cols, K);
     if (LB == kLayoutK) B.rows = min(B.rows, K); else B.cols = min(B.cols, K);
   }
-  WaveAcc<float, WN> acc;
+  constexpr int NB = 2;  // MFMA blocks of a wave, per side
+  SplitAcc<Planes<SA>::n, Planes<SB>::n> acc;
   acc.zero();
-  tile_mma<float, SA, LA, SB, LB, WN>(acc, A, B, m0, n0, K, sa0, sa1, sb0, sb1, P.sym && ti == tj);
+  split_mma<true, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, P.sym && ti == tj);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool diag = P.sym && ti == tj;
@@ -216,7 +208,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
   // upper-right square (block rows of its top and bottom halves)
   const bool helper = diag && wave == 2;
   const int wm0 = m0 + (helper ? 0 : (wave >> 1) * kWaveTile),
-            wn0 = n0 + (helper ? kWaveTile : (wave & 1) * kWaveTile * WN);
+            wn0 = n0 + (helper ? kWaveTile : (wave & 1) * kWaveTile);
   typedef Mfma<float> F;
   if constexpr (!std::is_same<SGG, void>::value) {
     // plain outputs only (preconditioning); P.gD set: P with the fused graft
@@ -225,25 +217,24 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
     {
       __shared__ double gred[kThreads / 64];
       float smg = 0.f, sps = 0.f;
-      const bool vec = m0 + kTile <= P.M && n0 + TN <= P.N && (P.ldc & 3) == 0 && (P.ldg & 3) == 0 &&
+      const bool vec = m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 && (P.ldg & 3) == 0 &&
                        (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 && (reinterpret_cast<uintptr_t>(P.gD) & 15) == 0 &&
                        (reinterpret_cast<uintptr_t>(P.gG) & (4 * sizeof(SGG) - 1)) == 0;
-      const bool rows16 = m0 + kTile <= P.M && n0 + TN <= P.N && (P.ldc & 3) == 0 &&
+      const bool rows16 = m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 &&
                           (reinterpret_cast<uintptr_t>(P.C) & 15) == 0;
       // a block row of the wave's accumulators (64 columns at a time) goes
       // through the wave's own LDS slice; the graft work then walks it row by
       // row (rolled loops, so the epilogue keeps the main loop's register
       // budget)
-      float* epi = reinterpret_cast<float*>(wave == 0 ? sa0 : (wave == 1 ? sa1 : (wave == 2 ? sb0 : sb1)));
+      float* epi = reinterpret_cast<float*>(smem + wave * 8192);
 #pragma unroll
-      for (int ih = 0; ih < WaveAcc<float>::NB * WN; ++ih) {
-        const int i = ih / WN, h = ih % WN;
+      for (int i = 0; i < NB; ++i) {
 #pragma unroll
-        for (int j = 0; j < WaveAcc<float>::NB; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
           for (int v = 0; v < F::kAcc; ++v)
-            epi[F::row(lane, v) * kWaveTile + j * F::kM + F::col(lane)] = P.alpha * acc.c[i][h * WaveAcc<float>::NB + j][v];
-        const int r0 = wm0 + i * F::kM, c0 = wn0 + h * kWaveTile;
+            epi[F::row(lane, v) * kWaveTile + j * F::kM + F::col(lane)] = P.alpha * acc.c[i][j][v];
+        const int r0 = wm0 + i * F::kM, c0 = wn0;
         if (!graft && rows16) {
           epi_rows(epi, P.C + (int64_t)r0 * P.ldc + c0, P.ldc, lane);
         } else if (!graft) {
@@ -301,19 +292,17 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
       return;
     }
   }
-#if SHP_EPI_VEC
   // Symmetric output, off-diagonal full tile: mirrored values go out as
   // 16-byte stores (a lane's 4 consecutive rows are 4 consecutive columns of
   // the transposed tile).  The old output is symmetric too, so the four old
   // values of rows r..r+3, column c are one 16-byte load of row c (the
   // mirror this lane then overwrites; no other lane or workgroup touches it).
-  if constexpr (WN == 1)
   if (P.sym && !diag && m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 &&
       (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
 #pragma unroll
-    for (int i = 0; i < WaveAcc<float>::NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < WaveAcc<float>::NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int g = 0; g < F::kAcc / 4; ++g) {
           const int r = wm0 + i * F::kM + F::row(lane, 4 * g);
@@ -336,20 +325,19 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
   // (not compiled into the row x row instantiation, which only forms
   // symmetric statistics and would lose an occupancy step to it).
   if constexpr (!(LA == kLayoutRow && LB == kLayoutRow))
-  if (!P.sym && m0 + kTile <= P.M && n0 + TN <= P.N && (P.ldc & 3) == 0 &&
+  if (!P.sym && m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 &&
       (reinterpret_cast<uintptr_t>(P.C) & 15) == 0) {
-    float* epi = reinterpret_cast<float*>(wave == 0 ? sa0 : (wave == 1 ? sa1 : (wave == 2 ? sb0 : sb1)));
+    float* epi = reinterpret_cast<float*>(smem + wave * 8192);
 #pragma unroll
-    for (int ih = 0; ih < WaveAcc<float>::NB * WN; ++ih) {
-      const int i = ih / WN, h = ih % WN;
-      const int c0 = wn0 + h * kWaveTile;
+    for (int i = 0; i < NB; ++i) {
+      const int c0 = wn0;
 #pragma unroll
-      for (int j = 0; j < WaveAcc<float>::NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int v = 0; v < F::kAcc; ++v) {
           const int r = wm0 + i * F::kM + F::row(lane, v);
           const int c = c0 + j * F::kM + F::col(lane);
-          float x = P.alpha * acc.c[i][h * WaveAcc<float>::NB + j][v];
+          float x = P.alpha * acc.c[i][j][v];
           if (P.beta != 0.f) x += P.beta * gload<float>(P.C + (int64_t)r * P.ldc + c);
           epi[F::row(lane, v) * kWaveTile + j * F::kM + F::col(lane)] = x;
         }
@@ -357,17 +345,16 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const
     }
     return;
   }
-#endif
 #pragma unroll
-  for (int i = 0; i < WaveAcc<float>::NB; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < WaveAcc<float, WN>::NBJ; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < F::kAcc; ++v) {
         const int r = wm0 + i * F::kM + F::row(lane, v);
         const int c = wn0 + j * F::kM + F::col(lane);
-        if (diag && wave == 1 && i >= WaveAcc<float>::NB / 2) continue;
-        if (helper && i < WaveAcc<float>::NB / 2) continue;
+        if (diag && wave == 1 && i >= NB / 2) continue;
+        if (helper && i < NB / 2) continue;
         if (r >= P.M || c >= P.N) continue;
         if (diag && r > c) continue;
         float x = P.alpha * acc.c[i][j][v];
@@ -609,6 +596,33 @@ __global__ __launch_bounds__(kThreads) void tile_list_kernel(const RootState* __
   build_tile_list(st, njobs, tmap, ubegin, diag_last, tlist, tcount);
 }
 
+// Tile product of the root kernels in either precision.
+template <typename T, int LA, int LB>
+struct RootProduct;
+template <int LA, int LB>
+struct RootProduct<float, LA, LB> {
+  typedef SplitAcc<3, 3> Acc;
+  static constexpr int bytes = SplitShm<float, float>::bytes;
+  static __device__ __forceinline__ void run(Acc& acc, const Operand<float>& A, const Operand<float>& B, int m0,
+                                             int n0, int K, char* smem, bool diag) {
+    acc.zero();
+    // a non-finite iterate stops its matrix (DIVERGED) whatever it holds
+    split_mma<false, float, LA, float, LB>(acc, A, B, m0, n0, K, smem, diag);
+  }
+};
+template <int LA, int LB>
+struct RootProduct<double, LA, LB> {
+  typedef WaveAcc<double> Acc;
+  static constexpr int bytes = 16;
+  static __device__ __forceinline__ void run(Acc& acc, const Operand<double>& A, const Operand<double>& B, int m0,
+                                             int n0, int K, char*, bool diag) {
+    __shared__ __attribute__((aligned(16))) double a0[StageElems<double, LA>::value], a1[StageElems<double, LA>::value];
+    __shared__ __attribute__((aligned(16))) double b0[StageElems<double, LB>::value], b1[StageElems<double, LB>::value];
+    acc.zero();
+    tile_mma<double, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, diag);
+  }
+};
+
 // tlist / tcount: the compact upper-tile list of the matrices still active
 // (build_tile_list: early tiles, then any late diagonal ones); the grid is
 // sized for every upper tile (plus the slack of xcd_split_remap), and the
@@ -618,13 +632,12 @@ __global__ __launch_bounds__(kThreads) void tile_list_kernel(const RootState* __
 // before its share of the late, cheaper diagonal ones (of the matrices of
 // its own range), which evens out when its compute units finish.
 template <typename T>
-__global__ __launch_bounds__(kThreads, MinWaves<T>::value) void newton_stage_kernel(const NewtonJob<T>* __restrict__ jobs,
+__global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const NewtonJob<T>* __restrict__ jobs,
                                                                const uint32_t* __restrict__ tlist,
                                                                const int* __restrict__ tcount, int njobs,
                                                                RootState* __restrict__ st, NewtonStage S,
                                                                int mixed) {
-  __shared__ __attribute__((aligned(16))) T sa0[StageElems<T, kLayoutK>::value], sa1[StageElems<T, kLayoutK>::value];
-  __shared__ __attribute__((aligned(16))) T sb0[StageElems<T, kLayoutK>::value], sb1[StageElems<T, kLayoutK>::value];
+  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutK, kLayoutK>::bytes];
   const int np = S.nprod;
   const int nt = tcount[0], ne = tcount[1];
   int l;
@@ -662,10 +675,11 @@ __global__ __launch_bounds__(kThreads, MinWaves<T>::value) void newton_stage_ker
   Operand<T> A{pa, n, n, n, al};
   Operand<T> B{pb, n, n, n, al};
 
-  WaveAcc<T> acc;
-  acc.zero();
-  // All operands are symmetric, so both are read k-major (storage row = k).
-  tile_mma<T, T, kLayoutK, T, kLayoutK>(acc, A, B, m0, n0, n, sa0, sa1, sb0, sb1, ti == tj);
+  // All operands are symmetric, so both may be read in either layout: fp32
+  // row-wise (k contiguous, as its LDS fragments are), fp64 k-major.
+  constexpr int L = sizeof(T) == 4 ? kLayoutRow : kLayoutK;
+  typename RootProduct<T, L, L>::Acc acc;
+  RootProduct<T, L, L>::run(acc, A, B, m0, n0, n, smem, ti == tj);
   // value of output element (r, c) from its accumulator
   auto fin = [&](T v, int r, int c) -> T {
     T x = ca * v;
@@ -689,7 +703,6 @@ __global__ __launch_bounds__(kThreads, MinWaves<T>::value) void newton_stage_ker
       rmax = rmax > d ? rmax : d;
     }
   };
-#if SHP_EPI_VEC
   // Off-diagonal full tile of an fp32 product: the 4 consecutive rows a lane
   // holds (v = 4g .. 4g+3) are 4 consecutive columns of the mirrored tile,
   // written as one 16-byte store.
@@ -720,7 +733,6 @@ __global__ __launch_bounds__(kThreads, MinWaves<T>::value) void newton_stage_ker
           gstore<f4>(reinterpret_cast<float*>(pc) + (int64_t)c * n + r, w);
         }
   } else
-#endif
   {
 #pragma unroll
     for (int i = 0; i < WaveAcc<T>::NB; ++i)
@@ -763,8 +775,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_dense_kernel(const
                                                                           const int* __restrict__ tcount,
                                                                           int njobs, RootState* __restrict__ st,
                                                                           NewtonStage S, int mixed) {
-  __shared__ __attribute__((aligned(16))) T sa0[StageElems<T, kLayoutRow>::value], sa1[StageElems<T, kLayoutRow>::value];
-  __shared__ __attribute__((aligned(16))) T sb0[StageElems<T, kLayoutK>::value], sb1[StageElems<T, kLayoutK>::value];
+  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutRow, kLayoutK>::bytes];
   const int np = S.nprod;
   const int nwork = np * *tcount;
   int l;
@@ -802,9 +813,8 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_dense_kernel(const
   Operand<T> A{pa, n, n, n, al};
   Operand<T> B{pb, n, n, n, al};
 
-  WaveAcc<T> acc;
-  acc.zero();
-  tile_mma<T, T, kLayoutRow, T, kLayoutK>(acc, A, B, m0, n0, n, sa0, sa1, sb0, sb1);
+  typename RootProduct<T, kLayoutRow, kLayoutK>::Acc acc;
+  RootProduct<T, kLayoutRow, kLayoutK>::run(acc, A, B, m0, n0, n, smem, false);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = m0 + (wave >> 1) * kWaveTile, wn0 = n0 + (wave & 1) * kWaveTile;

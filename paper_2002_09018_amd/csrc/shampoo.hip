@@ -270,12 +270,12 @@ constexpr int kDiagLastMaxPerXcd = 128;
 // share the slabs of G they read in L2.
 constexpr int kDiagLastMinK = 2048;
 
-template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void, int WN = 1>
+template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
 shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t s, int cls) {
   if (probs.empty()) return SHAMPOO_OK;
   int total = 0, mixed = 0, sym = 1;
   for (auto& p : probs) {
-    p.tiles_n = cdiv(p.N, kTile * WN);  // WN = 2: 256-wide tile columns (plain outputs only)
+    p.tiles_n = cdiv(p.N, kTile);
     p.tile_begin = total;
     total += p.sym ? p.tiles_n * (p.tiles_n + 1) / 2 : cdiv(p.M, kTile) * p.tiles_n;
     mixed |= p.M != probs[0].M || p.N != probs[0].N || p.K != probs[0].K;
@@ -293,7 +293,7 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
                                          : total;
   const void* d = nullptr;
   STATUS_TRY(upload_table(h, probs.data(), probs.size() * sizeof(GemmProblem), s, &d));
-  auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG, WN>;
+  auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG>;
   const int lds = 0;  // static LDS
   const int np = (int)probs.size();
   STATUS_TRY(launch(h, cls, s, [&] {
@@ -321,11 +321,9 @@ shampoo_status check_blocks(Handle* h, const shampoo_block* blocks, int nblocks,
 template <typename SG>
 shampoo_status stats_impl(Handle* h, const shampoo_block* blocks, int nb, float beta2, hipStream_t s) {
   const float c = beta2 == 1.0f ? 1.0f : 1.0f - beta2;
-  const int ve = 16 / (int)sizeof(SG);
   std::vector<GemmProblem> left, right;
   for (int i = 0; i < nb; ++i) {
     const shampoo_block& b = blocks[i];
-    const bool al = aligned16(b.G) && (b.ld % ve) == 0;
     if (b.L) {
       GemmProblem p{};
       p.A = b.G; p.B = b.G; p.C = b.L;
@@ -333,7 +331,6 @@ shampoo_status stats_impl(Handle* h, const shampoo_block* blocks, int nb, float 
       p.a_rows = p.b_rows = b.rows; p.a_cols = p.b_cols = b.cols;
       p.M = p.N = b.rows; p.K = b.cols;
       p.alpha = c; p.beta = beta2; p.sym = 1;
-      p.a_aligned = p.b_aligned = al;
       left.push_back(p);
     }
     if (b.R) {
@@ -343,7 +340,6 @@ shampoo_status stats_impl(Handle* h, const shampoo_block* blocks, int nb, float 
       p.a_rows = p.b_rows = b.rows; p.a_cols = p.b_cols = b.cols;
       p.M = p.N = b.cols; p.K = b.rows;
       p.alpha = c; p.beta = beta2; p.sym = 1;
-      p.a_aligned = p.b_aligned = al;
       right.push_back(p);
     }
   }
@@ -437,22 +433,12 @@ std::vector<int> precond_groups(const shampoo_block* blocks, int nb) {
 template <typename SG>
 shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipStream_t s, bool fuse_graft = false,
                             float eta0 = 0.f, float* norms = nullptr) {
-  const int ve = 16 / (int)sizeof(SG);
   std::vector<GemmProblem> g_rr, lr_z, lr_g;
   std::vector<int> g_rr_b, lr_z_b, lr_g_b;  // block of each problem (ascending)
   // graft: per block, the first and the number of norm partials (the P
   // GEMM's output tiles)
   std::vector<int> pbegin(nb), pcount(nb);
   int ptotal = 0;
-  // Without the fused graft, the products by Lr (P = Lr G, or Lr Z) run on
-  // 128 x 256 tiles when every block with Lr has a width that is a multiple
-  // of 256 (C2: 126 -> 132 TFLOP/s; fewer operand bytes per flop).  G Rr, and
-  // every GEMM with the fused graft, keep 128 x 128: the wide kernel runs two
-  // workgroups per CU, which hides the graft epilogue less than four
-  // (measured: no gain).
-  bool wide = !fuse_graft;
-  for (int i = 0; i < nb; ++i)
-    if (blocks[i].Lr && blocks[i].cols % (2 * kTile) != 0) wide = false;
   if (fuse_graft) {
     for (int i = 0; i < nb; ++i) {
       pbegin[i] = ptotal;
@@ -476,22 +462,21 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
   size_t zoff = 0;
   for (int i = 0; i < nb; ++i) {
     const shampoo_block& b = blocks[i];
-    const bool gal = aligned16(b.G) && (b.ld % ve) == 0;
     if (b.Lr && b.Rr) {
       float* Z = reinterpret_cast<float*>(static_cast<char*>(h->zbuf) + zoff);
       zoff += align256((size_t)b.rows * b.cols * sizeof(float));
       GemmProblem p{};  // Z = G Rr
-      p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols; p.a_aligned = gal;
+      p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols;
       p.B = b.Rr; p.ldb = b.cols; p.b_rows = b.cols; p.b_cols = b.cols;
-      p.b_aligned = aligned16(b.Rr) && (b.cols % 4) == 0;
+     
       p.C = Z; p.ldc = b.cols; p.M = b.rows; p.N = b.cols; p.K = b.cols;
       p.alpha = 1.f; p.beta = 0.f;
       g_rr.push_back(p);
       g_rr_b.push_back(i);
       GemmProblem q{};  // P = Lr Z, Lr symmetric: read k-major
       q.A = b.Lr; q.lda = b.rows; q.a_rows = b.rows; q.a_cols = b.rows;
-      q.a_aligned = aligned16(b.Lr) && (b.rows % 4) == 0;
-      q.B = Z; q.ldb = b.cols; q.b_rows = b.rows; q.b_cols = b.cols; q.b_aligned = (b.cols % 4) == 0;
+     
+      q.B = Z; q.ldb = b.cols; q.b_rows = b.rows; q.b_cols = b.cols;
       q.C = b.P; q.ldc = b.ld; q.M = b.rows; q.N = b.cols; q.K = b.rows;
       q.alpha = 1.f; q.beta = 0.f;
       with_graft(q, b, i);
@@ -499,9 +484,9 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
       lr_z_b.push_back(i);
     } else if (b.Rr) {
       GemmProblem p{};  // P = G Rr
-      p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols; p.a_aligned = gal;
+      p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols;
       p.B = b.Rr; p.ldb = b.cols; p.b_rows = b.cols; p.b_cols = b.cols;
-      p.b_aligned = aligned16(b.Rr) && (b.cols % 4) == 0;
+     
       p.C = b.P; p.ldc = b.ld; p.M = b.rows; p.N = b.cols; p.K = b.cols;
       p.alpha = 1.f; p.beta = 0.f;
       with_graft(p, b, i);
@@ -510,8 +495,8 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
     } else if (b.Lr) {
       GemmProblem q{};  // P = Lr G
       q.A = b.Lr; q.lda = b.rows; q.a_rows = b.rows; q.a_cols = b.rows;
-      q.a_aligned = aligned16(b.Lr) && (b.rows % 4) == 0;
-      q.B = b.G; q.ldb = b.ld; q.b_rows = b.rows; q.b_cols = b.cols; q.b_aligned = gal;
+     
+      q.B = b.G; q.ldb = b.ld; q.b_rows = b.rows; q.b_cols = b.cols;
       q.C = b.P; q.ldc = b.ld; q.M = b.rows; q.N = b.cols; q.K = b.rows;
       q.alpha = 1.f; q.beta = 0.f;
       with_graft(q, b, i);
@@ -576,13 +561,8 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
     return tables_done(h, s);
   }
   STATUS_TRY((run_gemm<SG, kLayoutRow, float, kLayoutK>(h, g_rr, s, SHAMPOO_KCLASS_PRECOND)));
-  if (wide) {
-    STATUS_TRY((run_gemm<float, kLayoutK, float, kLayoutK, false, void, 2>(h, lr_z, s, SHAMPOO_KCLASS_PRECOND)));
-    STATUS_TRY((run_gemm<float, kLayoutK, SG, kLayoutK, false, void, 2>(h, lr_g, s, SHAMPOO_KCLASS_PRECOND)));
-  } else {
-    STATUS_TRY((run_gemm<float, kLayoutK, float, kLayoutK>(h, lr_z, s, SHAMPOO_KCLASS_PRECOND)));
-    STATUS_TRY((run_gemm<float, kLayoutK, SG, kLayoutK>(h, lr_g, s, SHAMPOO_KCLASS_PRECOND)));
-  }
+  STATUS_TRY((run_gemm<float, kLayoutK, float, kLayoutK>(h, lr_z, s, SHAMPOO_KCLASS_PRECOND)));
+  STATUS_TRY((run_gemm<float, kLayoutK, SG, kLayoutK>(h, lr_g, s, SHAMPOO_KCLASS_PRECOND)));
   if (!copy.empty()) {
     int total = 0;
     std::vector<GraftBlock> tb = graft_table(copy.data(), (int)copy.size(), &total);
@@ -1761,7 +1741,6 @@ shampoo_status shampoo_embedding_stats(void* handle, const float* U, const int32
   DeviceGuard g(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const float c = beta2 == 1.0f ? 1.0f : 1.0f - beta2;
-  const bool al = aligned16(U) && (dim % 4) == 0;
   const size_t pstride = align256((size_t)dim * dim * sizeof(float)) / sizeof(float);
   float* part = L.splits > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + L.part) : nullptr;
   std::vector<GemmProblem> probs;
@@ -1772,7 +1751,6 @@ shampoo_status shampoo_embedding_stats(void* handle, const float* U, const int32
     p.a_rows = p.b_rows = nnz; p.a_cols = p.b_cols = dim;
     p.M = p.N = dim; p.K = nnz;
     p.sym = 1;
-    p.a_aligned = p.b_aligned = al;
     p.kcount = count; p.koff = q; p.ksplit = L.splits;  // split q of the active rows
     if (part) {
       p.C = part + (size_t)q * pstride; p.ldc = dim; p.alpha = 1.f; p.beta = 0.f;
@@ -1805,8 +1783,8 @@ shampoo_status shampoo_embedding_precondition(void* handle, const float* U, cons
   std::vector<GemmProblem> probs(1);
   GemmProblem& p = probs[0];
   p = GemmProblem{};
-  p.A = U; p.lda = dim; p.a_rows = nnz; p.a_cols = dim; p.a_aligned = aligned16(U) && (dim % 4) == 0;
-  p.B = Rr; p.ldb = dim; p.b_rows = dim; p.b_cols = dim; p.b_aligned = aligned16(Rr) && (dim % 4) == 0;
+  p.A = U; p.lda = dim; p.a_rows = nnz; p.a_cols = dim;
+  p.B = Rr; p.ldb = dim; p.b_rows = dim; p.b_cols = dim;
   p.C = P; p.ldc = dim; p.M = nnz; p.N = dim; p.K = dim;
   p.alpha = 1.f; p.beta = 0.f;
   p.mcount = count;

@@ -1,0 +1,132 @@
+"""fp32 products on the bf16 matrix cores (three-plane split): statistics and
+preconditioning at the edges of tiles, stages and accumulation runs, on
+contiguous and on oddly strided (unaligned) views, against fp64 products of
+the same inputs, and the handling of infinities, NaN and values that round up
+to infinity in bf16.
+
+Bound, per output element with s = sum |a||b| (fp64): a 16-deep step rounds
+at most 12 times at a magnitude of at most s; over the first 256 k ten of the
+twelve only at the magnitude of the smaller products (below 2^-7 s), later
+runs of 256 k are added once each; the dropped products are below 2^-25 s:
+  |err| <= (2.1 steps(min(K, 256)) + [K > 256] (192 + K / 256) + 4) 2^-24 s.
+"""
+import numpy as np
+import pytest
+
+from tests.gpu_util import gpu_env, host, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch, B, dev = gpu_env()
+    h = B.shampoo_create(0)
+    yield torch, B, dev, h
+    B.shampoo_destroy(h)
+
+
+def _view(torch, dev, x, pad, off, dtype):
+    """x as a view with row stride cols + pad, starting `off` elements into its buffer."""
+    m, n = x.shape
+    buf = torch.zeros(off + m * (n + pad), device=dev, dtype=dtype)
+    v = buf[off:].view(m, n + pad)[:, :n]
+    v.copy_(to_dev(torch, x, dev))
+    return v
+
+
+def _bound(K, s):
+    units = 2.1 * -(-min(K, 256) // 16) + (192 + K / 256 if K > 256 else 0) + 4
+    return units * 2.0 ** -24 * s + 1e-37
+
+
+SIZES = [(1, 1), (1, 300), (3, 17), (16, 16), (31, 33), (127, 15), (128, 16), (129, 257), (130, 256), (257, 130),
+         (200, 513)]
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("pad,off", [(0, 0), (3, 1)])
+def test_stats_edges(env, bf16, pad, off):
+    torch, B, dev, h = env
+    dt = torch.bfloat16 if bf16 else torch.float32
+    r = np.random.default_rng(7)
+    blocks, want = [], []
+    for m, n in SIZES:
+        g = (r.standard_normal((m, n)) * np.exp(r.uniform(-6, 6, (m, 1)))).astype(np.float32)
+        G = _view(torch, dev, g, pad, off, dt)
+        x = host(G.float().contiguous()).astype(np.float64)
+        L = torch.zeros(m, m, device=dev)
+        R = torch.zeros(n, n, device=dev)
+        blocks.append(B.Block(G=G, L=L, R=R))
+        want.append(x)
+    say(f"stats edges bf16={bf16} pad={pad}")
+    B.shampoo_update_stats(h, blocks)
+    torch.cuda.synchronize()
+    for b, x in zip(blocks, want):
+        for got, a in ((b.L, x), (b.R, x.T)):
+            got = host(got).astype(np.float64)
+            assert np.array_equal(got, got.T)
+            share = float((np.abs(got - a @ a.T) / _bound(a.shape[1], np.abs(a) @ np.abs(a).T)).max())
+            assert share <= 1.0, (x.shape, share)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("pad,off", [(0, 0), (3, 1)])
+def test_precondition_edges(env, bf16, pad, off):
+    torch, B, dev, h = env
+    dt = torch.bfloat16 if bf16 else torch.float32
+    r = np.random.default_rng(11)
+    blocks, want = [], []
+    for i, (m, n) in enumerate(SIZES):
+        G = _view(torch, dev, r.standard_normal((m, n)).astype(np.float32), pad, off, dt)
+        P = _view(torch, dev, np.zeros((m, n), np.float32), pad, off, torch.float32)
+        left, right = [(True, True), (True, False), (False, True)][i % 3]
+        l, q = (0.5 * (a + a.T) for a in (r.standard_normal((m, m)), r.standard_normal((n, n))))
+        Lr = to_dev(torch, l.astype(np.float32), dev) if left else None
+        Rr = to_dev(torch, q.astype(np.float32), dev) if right else None
+        blocks.append(B.Block(G=G, P=P, Lr=Lr, Rr=Rr))
+    say(f"precondition edges bf16={bf16} pad={pad}")
+    B.shampoo_precondition(h, blocks)
+    torch.cuda.synchronize()
+    for b in blocks:
+        x = host(b.G.float().contiguous()).astype(np.float64)
+        m, n = x.shape
+        s = np.abs(x)
+        bound = np.zeros_like(x)
+        if b.Rr is not None:
+            q = host(b.Rr).astype(np.float64)
+            bound = _bound(n, s @ np.abs(q)) + 2.0 ** -24 * (s @ np.abs(q))
+            x, s = x @ q, s @ np.abs(q)
+        if b.Lr is not None:
+            l = host(b.Lr).astype(np.float64)
+            bound = np.abs(l) @ bound + _bound(m, np.abs(l) @ s)
+            x = l @ x
+        share = float((np.abs(host(b.P.contiguous()).astype(np.float64) - x) / bound).max())
+        assert share <= 1.0, (x.shape, share)
+
+
+@pytest.mark.parametrize("m,n", [(40, 70), (300, 200)])
+def test_non_finite(env, m, n):
+    """An output is what the fp32 sum gives: infinite or NaN only where an
+    infinity, a NaN or an overflow enters it, finite elsewhere."""
+    torch, B, dev, h = env
+    r = np.random.default_rng(3)
+    g = r.uniform(0.5, 1.0, (m, n)).astype(np.float32)
+    g[1, 2] = np.inf
+    g[m - 1, 5] = np.nan
+    g[7, n - 1] = 3.4e38  # rounds to infinity in bf16
+    G = to_dev(torch, g, dev)
+    L, R = torch.zeros(m, m, device=dev), torch.zeros(n, n, device=dev)
+    say(f"non-finite {m}x{n}")
+    B.shampoo_update_stats(h, [B.Block(G=G, L=L, R=R)])
+    torch.cuda.synchronize()
+    x = g.astype(np.float64)
+    for got, a in ((L, x), (R, x.T)):
+        want = a @ a.T
+        want[np.abs(want) > 3.5e38] = np.inf  # the largest finite sum here is about 3.4e38
+        got = host(got).astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(np.isinf(got), np.isinf(want))
+        f = np.isfinite(want)
+        share = float((np.abs(got[f] - want[f]) / (1e-5 * np.abs(want[f]))).max())
+        assert share <= 1.0, share
