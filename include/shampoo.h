@@ -292,8 +292,10 @@ shampoo_status shampoo_graft(void* handle, const shampoo_block* blocks, int nblo
  * and its launches are not recorded by shampoo_timing_*.
  * Limits: nblocks <= SHAMPOO_GRAFT_NOALLOC_MAX_BLOCKS and at most
  * SHAMPOO_GRAFT_NOALLOC_MAX_CHUNKS chunks in total, where a block of
- * m x n has ceil(m / max(1, 16384 / n)) chunks (C2's 96 blocks of
- * 1024 x 4096 take 24576); beyond either, ENOMEM and nothing is enqueued.
+ * m x n has ceil(m / max(1, 16384 / n)) chunks (96 blocks of 1024 x 4096
+ * take 24576; calls of fewer than 2^24 elements use smaller chunks, about
+ * 1024 to 2048 plus one per block); beyond either, ENOMEM and nothing is
+ * enqueued.
  * Every call on a GPU uses that GPU's one array: calls on one stream are
  * ordered, calls that overlap on different streams of one GPU race.  The
  * host waits, if needed, for the previous call's table copy out of the

@@ -1850,29 +1850,39 @@ __device__ inline int scalar_iters(double m, int p, double tol, int cap) {
   return k;
 }
 
+// One wave per matrix.  The smallest m0 that converges within the iteration
+// count is bracketed by 64-way multisection in the logarithm (a one-thread
+// bisection of 40 steps cost 32 us at 4 iterations and 118 us at 19; 8 rounds
+// of 64 points cover the same 1e30^(2^-40)).
 template <typename T>
-__global__ void root_info_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs, const RootState* __restrict__ st,
-                                 int p, float tol, void* __restrict__ info_out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= njobs) return;
+__global__ __launch_bounds__(64) void root_info_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs,
+                                                       const RootState* __restrict__ st, int p, float tol,
+                                                       void* __restrict__ info_out) {
+  const int j = blockIdx.x, lane = threadIdx.x;
   const RootState& s = st[j];
   // condition estimate from the iteration count
   double kappa = 0.0;
   if ((s.status == kConverged || s.status == kStagnated) && s.warm != 1) {
     const double tl = fmax((double)tol, (double)s.resid);
-    double lo = 1e-30, hi = 1.0;  // N(lo) > iters >= N(hi) (N decreasing on (0, 1])
-    // only N(m) <= iters is asked: counting stops at iters + 1
+    // N(10^lo) > iters >= N(10^hi) (N decreasing on (0, 1]); only
+    // N(m) <= iters is asked: counting stops at iters + 1
     const int cap = s.iters + 1;
-    if (scalar_iters(lo, p, tl, cap) <= s.iters) {
+    double lo = -30.0, hi = 0.0;
+    if (scalar_iters(1e-30, p, tl, cap) <= s.iters) {
       kappa = 1.0;
     } else {
-      for (int b = 0; b < 40; ++b) {  // hi / lo = 1e30^(2^-40) < 1 + 1e-10
-        const double mid = sqrt(lo * hi);
-        if (scalar_iters(mid, p, tl, cap) <= s.iters) hi = mid; else lo = mid;
+      for (int b = 0; b < 8; ++b) {  // 30 / 65^8 < 1e-13 decades
+        const double w = (hi - lo) / 65.0;
+        const bool in = scalar_iters(exp10(lo + w * (lane + 1)), p, tl, cap) <= s.iters;
+        const unsigned long long m = __ballot(in);
+        const int f = m ? __ffsll(m) - 1 : 64;  // points below the first one in stay out
+        hi = f < 64 ? lo + w * (f + 1) : hi;
+        lo = lo + w * f;
       }
-      kappa = (1.0 + p) / (2.0 * hi);
+      kappa = (1.0 + p) / (2.0 * exp10(hi));
     }
   }
+  if (lane != 0) return;
   int32_t* io = reinterpret_cast<int32_t*>(info_out) + 8 * j;
   float* fo = reinterpret_cast<float*>(io);
   io[0] = s.status;
@@ -1927,23 +1937,30 @@ __device__ __forceinline__ int find_block_graft(const GraftBlock* b, int nb, int
 
 // Calls f(ig, iw, w) for the elements of a chunk (rows r0..r1 of a block):
 // ig is the offset in G and P, iw the offset in W, D, Mg and Ps; 4-wide
-// (w = 4) where the block allows vector access, else scalar (w = 1).  Whole
-// rows per chunk keep index arithmetic free of divisions.
+// (w = 4) where the block allows vector access, else scalar (w = 1).  Rows
+// narrower than the workgroup are walked several at a time (a power of two of
+// threads per row): with one row at a time, a chunk of 128 rows of 128 columns
+// kept 32 threads busy for 128 dependent round trips (pass 2 36 us; a call of
+// 13 blocks of 64 to 517 columns with momentum spent 435 us in pass 1).
 template <typename F>
 __device__ __forceinline__ void for_chunk(const GraftBlock& B, int r0, int r1, F&& f) {
   if (B.count) r1 = min(r1, *B.count);
-  for (int r = r0; r < r1; ++r) {
+  const int w = B.vec4 ? 4 : 1;
+  const int units = B.vec4 ? B.cols >> 2 : B.cols;  // accesses per row
+  int sh = 8;                                       // log2 of the threads per row
+  while (sh > 0 && (1 << (sh - 1)) >= units) --sh;
+  const int c0 = threadIdx.x & ((1 << sh) - 1);
+  for (int r = r0 + (int)(threadIdx.x >> sh); r < r1; r += kThreads >> sh) {
     int64_t wr = r;
     if (B.wrows) {
       wr = B.wrows[r];
       if (wr < 0 || wr >= B.wlimit) continue;
     }
     const int64_t g0 = (int64_t)r * B.ld, w0 = wr * B.ldw;
-    if (B.vec4) {
-      const int c4 = B.cols >> 2;
-      for (int c = threadIdx.x; c < c4; c += kThreads) f(g0 + 4 * c, w0 + 4 * c, 4);
+    if (w == 4) {
+      for (int c = c0; c < units; c += 1 << sh) f(g0 + 4 * c, w0 + 4 * c, 4);
     } else {
-      for (int c = threadIdx.x; c < B.cols; c += kThreads) f(g0 + c, w0 + c, 1);
+      for (int c = c0; c < units; c += 1 << sh) f(g0 + c, w0 + c, 1);
     }
   }
 }

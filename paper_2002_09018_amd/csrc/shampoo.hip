@@ -359,11 +359,12 @@ int fill_graft_table(const shampoo_block* blocks, int nb, GraftBlock* out) {
   int t = 0;
   for (int i = 0; i < nb; ++i) {
     const shampoo_block& b = blocks[i];
+  const int chunk = graft_chunk_elems(blocks, nb);
     GraftBlock g{};
     g.G = b.G; g.W = b.W; g.D = b.D; g.P = b.P; g.Mg = b.Mg; g.Ps = b.Ps;
     g.ld = b.ld; g.rows = b.rows; g.cols = b.cols;
     g.ldw = b.ld; g.wrows = nullptr; g.count = nullptr; g.wlimit = b.rows;
-    g.rows_per_chunk = graft_rows_per_chunk(b.cols);
+    g.rows_per_chunk = graft_rows_per_chunk(b.cols, chunk);
     g.nchunks = cdiv(b.rows, g.rows_per_chunk);
     // 4-wide access needs every row start 16-byte aligned in every tensor
     // (G: 8-byte for bf16 is enough since it is read 4 elements at a time)
@@ -1260,8 +1261,9 @@ shampoo_status shampoo_graft_noalloc(void* handle, const shampoo_block* blocks, 
     return fail(h, SHAMPOO_ENOMEM, "%d blocks exceed the allocation-free graft's limit of %d", nblocks,
                 kNoallocMaxBlocks);
   int64_t chunks = 0;
-  for (int i = 0; i < nblocks; ++i) chunks += cdiv(blocks[i].rows, graft_rows_per_chunk(blocks[i].cols));
+  for (int i = 0; i < nblocks; ++i) chunks += cdiv(blocks[i].rows, graft_rows_per_chunk(blocks[i].cols, chunk));
   if (chunks > kNoallocMaxChunks)
+  const int chunk = graft_chunk_elems(blocks, nblocks);
     return fail(h, SHAMPOO_ENOMEM, "%lld chunks exceed the allocation-free graft's limit of %d", (long long)chunks,
                 kNoallocMaxChunks);
   DeviceGuard g(h->device);
@@ -1592,9 +1594,9 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
   }
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
     if (j32)
-      hipLaunchKernelGGL(root_info_kernel<float>, dim3(nb1), dim3(64), 0, s, j32, njobs, st, p, prm->tol, (void*)info);
+      hipLaunchKernelGGL(root_info_kernel<float>, dim3(njobs), dim3(64), 0, s, j32, njobs, st, p, prm->tol, (void*)info);
     else
-      hipLaunchKernelGGL(root_info_kernel<double>, dim3(nb1), dim3(64), 0, s, j64, njobs, st, p, prm->tol, (void*)info);
+      hipLaunchKernelGGL(root_info_kernel<double>, dim3(njobs), dim3(64), 0, s, j64, njobs, st, p, prm->tol, (void*)info);
   }));
   return tables_done(h, s);
 }
