@@ -18,6 +18,7 @@
 #include "embedding.hpp"
 #include "kernels.hpp"
 #include "shampoo.h"
+#include "small_root.hpp"
 
 using namespace shp;
 
@@ -242,13 +243,6 @@ shampoo_status launch(Handle* h, int cls, hipStream_t s, F&& f) {
   return SHAMPOO_OK;
 }
 
-template <typename K>
-shampoo_status set_lds(Handle* h, K kernel, int bytes) {
-  HIP_TRY(h, hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  return SHAMPOO_OK;
-}
-
 // ---------------------------------------------------------------- GEMM
 // Diagonal tiles of a symmetric product launch (the Newton products through
 // build_tile_list, the statistics GEMM through kMapDiagLast) run last when
@@ -351,15 +345,24 @@ shampoo_status stats_impl(Handle* h, const shampoo_block* blocks, int nb, float 
 }
 
 // ---------------------------------------------------------------- elementwise block tables
-// Chunks of one block in the graft kernels: whole rows, at most 16384 elements.
-inline int graft_rows_per_chunk(int cols) { return std::max(1, 16384 / cols); }
+// Chunks of the graft kernels, one workgroup each: whole rows of one block, at
+// most 16384 elements where the call has 2^24 elements or more, fewer in
+// smaller calls so that about 1024 chunks share the work (a 128 x 128 block is
+// 16 chunks of 1024 elements, one pass of a workgroup each, instead of one
+// chunk of 16 passes on one compute unit).
+int graft_chunk_elems(const shampoo_block* blocks, int nb) {
+  int64_t e = 0;
+  for (int i = 0; i < nb; ++i) e += (int64_t)blocks[i].rows * blocks[i].cols;
+  return (int)std::min<int64_t>(16384, std::max<int64_t>(1024, e / 1024));
+}
+inline int graft_rows_per_chunk(int cols, int chunk) { return std::max(1, chunk / cols); }
 
 // Fills out[0..nb) with the graft table of the blocks; returns the chunk count.
 int fill_graft_table(const shampoo_block* blocks, int nb, GraftBlock* out) {
+  const int chunk = graft_chunk_elems(blocks, nb);
   int t = 0;
   for (int i = 0; i < nb; ++i) {
     const shampoo_block& b = blocks[i];
-  const int chunk = graft_chunk_elems(blocks, nb);
     GraftBlock g{};
     g.G = b.G; g.W = b.W; g.D = b.D; g.P = b.P; g.Mg = b.Mg; g.Ps = b.Ps;
     g.ld = b.ld; g.rows = b.rows; g.cols = b.cols;
@@ -1260,10 +1263,10 @@ shampoo_status shampoo_graft_noalloc(void* handle, const shampoo_block* blocks, 
   if (nblocks > kNoallocMaxBlocks)
     return fail(h, SHAMPOO_ENOMEM, "%d blocks exceed the allocation-free graft's limit of %d", nblocks,
                 kNoallocMaxBlocks);
+  const int chunk = graft_chunk_elems(blocks, nblocks);
   int64_t chunks = 0;
   for (int i = 0; i < nblocks; ++i) chunks += cdiv(blocks[i].rows, graft_rows_per_chunk(blocks[i].cols, chunk));
   if (chunks > kNoallocMaxChunks)
-  const int chunk = graft_chunk_elems(blocks, nblocks);
     return fail(h, SHAMPOO_ENOMEM, "%lld chunks exceed the allocation-free graft's limit of %d", (long long)chunks,
                 kNoallocMaxChunks);
   DeviceGuard g(h->device);
@@ -1438,6 +1441,19 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     tf.tcount = reinterpret_cast<int*>(ws + L.tcountf);
     tf.mixed = tl.mixed;
   }
+  // matrices whose whole fp32 iteration runs in one workgroup (largest first)
+  std::vector<int> small;
+  if (j32)
+    for (int j = 0; j < njobs; ++j)
+      if (jobs[j].n <= kSmallMax) small.push_back(j);
+  std::stable_sort(small.begin(), small.end(), [&](int x, int y) { return jobs[x].n > jobs[y].n; });
+  const bool all_small = (int)small.size() == njobs;
+  const int* dsmall = nullptr;
+  if (!small.empty()) {
+    const void* d = nullptr;
+    STATUS_TRY(upload_table(h, small.data(), small.size() * sizeof(int), s, &d));
+    dsmall = static_cast<const int*>(d);
+  }
   const int nb1 = cdiv(njobs, 64);
   const int tail_all = prec == SHAMPOO_PRECISION_FP64 ? 1 : 0;
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
@@ -1472,7 +1488,8 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       }));
     }
   }
-  STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
+  // (newton_small_kernel forms its own)
+  if (!all_small || warm || prm->eps_relative) STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
     if (j32) {
       hipLaunchKernelGGL(frob_kernel<float>, dim3(up), dim3(kThreads), 0, s, j32, njobs, st, up);
       hipLaunchKernelGGL(root_prep_kernel<float>, dim3(nb1), dim3(64), 0, s, j32, njobs, st, p, prm->eps_relative, eps);
@@ -1555,9 +1572,24 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       esc_n = cap;
     }
     int fails = -1;
-    if (warm && warm_aborts == 0)
-      fails = 0;  // every warm result was accepted: no cold start
-    else
+    const bool cold = !(warm && warm_aborts == 0);
+    if (!cold) fails = 0;  // every warm result was accepted: no cold start
+    if (cold && !small.empty()) {
+      SmallRootArgs q{};
+      q.p = p;
+      q.power = prm->scaling == SHAMPOO_SCALING_POWER4;
+      q.max_iters = cap;
+      q.eps_relative = prm->eps_relative;
+      q.esc_thr = esc;
+      q.esc_n = esc_n;
+      q.tol = prm->tol;
+      q.eps = eps;
+      STATUS_TRY(launch(h, SHAMPOO_KCLASS_NEWTON_F32, s, [&] {
+        hipLaunchKernelGGL(newton_small_kernel, dim3((unsigned)small.size()), dim3(kSmallThreads), 0, s, j32, dsmall,
+                           st, q);
+      }));
+    }
+    if (cold && !all_small)
       STATUS_TRY(newton_phase<float>(h, j32, tl, njobs, st, dcount, up, full, flat, prog, p, prm->scaling, prm->tol,
                                      cap, prm->poll, SHAMPOO_KCLASS_NEWTON_F32, esc, esc_n, s, &fails));
     if (prec == SHAMPOO_PRECISION_AUTO) {
@@ -1570,13 +1602,14 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       } else if (fails >= 0) {
         run64 = fails > 0;  // known from the last poll: no synchronisation
       } else {
-        // the phase ended at its cap with matrices still running
+        // no polled count: the phase ended at its cap with matrices still
+        // running, or every matrix was small
         HIP_TRY(h, hipMemcpyAsync(h->pinned + 2 * kCountRing + 2, esc_count, sizeof(int), hipMemcpyDeviceToHost, s));
         HIP_TRY(h, hipStreamSynchronize(s));
         run64 = h->pinned[2 * kCountRing + 2] > 0;
       }
     }
-    STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
+    if (!all_small) STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
       hipLaunchKernelGGL(root_output_kernel<float>, dim3(flat), dim3(kThreads), 0, s, j32, njobs, st, flat, 0, p);
     }));
   }

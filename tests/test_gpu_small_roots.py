@@ -1,0 +1,105 @@
+"""Roots of matrices of at most 128 x 128 (the whole iteration in one
+workgroup) at the edges of its 32 x 32 blocks, for every kind of product
+program (powers of two, odd, mixed bits), both start scalings and both kinds
+of damping, against the oracle; a zero-iteration start, a NOT_PD matrix and an
+escalated one; and a mixed call, whose small matrices must come out bit for
+bit as in a call of their own.
+
+Tolerance: each iteration's fp32 rounding (sqrt(n) 2^-24 of the iterate)
+amplified by the condition number and the order, iters p kappa sqrt(n) 2^-24
+relative (Frobenius).
+"""
+import numpy as np
+import pytest
+
+import oracle.shampoo_oracle as O
+from tests.gpu_util import gpu_env, host, rel, say, spd, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch, B, dev = gpu_env()
+    h = B.shampoo_create(0)
+    yield torch, B, dev, h
+    B.shampoo_destroy(h)
+
+
+def _roots(env, mats, **params):
+    torch, B, dev, h = env
+    As = [to_dev(torch, a.astype(np.float32), dev) for a in mats]
+    Xs = [torch.full_like(a, float("nan")) for a in As]
+    prm = B.shampoo_root_params_default(**params)
+    ws = torch.empty(B.shampoo_inv_root_workspace_bytes([a.shape[0] for a in mats], prm.precision),
+                     dtype=torch.uint8, device=dev)
+    info = torch.zeros(8 * len(mats), dtype=torch.int32, device=dev)
+    B.shampoo_inv_root_batched(h, As, Xs, prm, ws, info)
+    torch.cuda.synchronize()
+    return [host(x) for x in Xs], B.decode_root_info(info)
+
+
+SIZES = [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128]
+KAPPA = 40.0
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 6, 7, 8, 16])
+@pytest.mark.parametrize("scaling", [0, 1])
+def test_sizes_and_orders(env, p, scaling):
+    torch, B, dev, h = env
+    mats = [spd(n, KAPPA, 100 + n) for n in SIZES]
+    say(f"small roots p={p} scaling={scaling}")
+    xs, info = _roots(env, mats, p=p, scaling=scaling, precision=B.PRECISION_FP32)
+    for a, x, i in zip(mats, xs, info):
+        n = a.shape[0]
+        assert i["status"] in (B.ROOT_CONVERGED, B.ROOT_STAGNATED), (n, i)
+        assert np.array_equal(x, x.T)
+        err = rel(x, O.inv_root(a.astype(np.float64), p, 1e-6)[0])
+        assert err <= max(1, i["iters"]) * p * KAPPA * np.sqrt(n) * 2.0 ** -24, (n, err)
+
+
+def test_relative_damping_asymmetric_input(env):
+    """The root of the symmetric part, scaled damping, odd sizes."""
+    torch, B, dev, h = env
+    r = np.random.default_rng(5)
+    mats = [spd(n, KAPPA, n) + 1e-3 * r.standard_normal((n, n)) for n in (5, 40, 101)]
+    say("small roots relative damping")
+    xs, info = _roots(env, mats, p=4, eps=1e-2, eps_relative=1, precision=B.PRECISION_FP32)
+    for a, x, i in zip(mats, xs, info):
+        a = a.astype(np.float32).astype(np.float64)
+        s = 0.5 * (a + a.T)
+        lam = np.linalg.eigvalsh(s)[-1]
+        assert abs(i["lambda_max"] / lam - 1) < 0.05
+        w = O.inv_root(s, 4, i["eps_eff"])[0]
+        assert rel(x, w) <= i["iters"] * 4 * KAPPA * np.sqrt(len(a)) * 2.0 ** -24
+
+
+def test_outcomes_and_mixed_call(env):
+    torch, B, dev, h = env
+    n = 70
+    ill = spd(n, 1e7, 3)
+    bad = spd(n, 10.0, 4)
+    bad[3, 3] = -1.0
+    nan = spd(n, 10.0, 4)
+    nan[1, 2] = np.nan
+    # z A = I: p = 1 and a 1 x 1 matrix start converged
+    small = [np.array([[2.0]], np.float32), spd(n, 20.0, 6), ill, bad, nan, spd(128, 30.0, 7), spd(33, 5.0, 8)]
+    big = [spd(200, 30.0, 9), spd(300, 1e7, 10)]
+    say("small roots outcomes")
+    alone, ia = _roots(env, small, p=4)
+    mixed, im = _roots(env, big[:1] + small[:4] + big[1:] + small[4:], p=4)
+    order = [1, 2, 3, 4, 6, 7, 8]
+    for k, (x, i) in enumerate(zip(alone, ia)):
+        m, j = mixed[order[k]], im[order[k]]
+        assert i == j or (np.isnan(i["resid"]) and np.isnan(j["resid"])), (k, i, j)
+        if k not in (3, 4):
+            assert np.array_equal(x, m), k
+    assert ia[2]["precision"] == 64 and rel(alone[2], O.inv_root(ill.astype(np.float64), 4, 1e-6)[0]) <= 5e-3
+    assert ia[3]["status"] == B.ROOT_NOT_PD and ia[4]["status"] == B.ROOT_NOT_PD
+    for k in (0, 1, 5, 6):
+        a = small[k].astype(np.float64)
+        assert ia[k]["precision"] == 32 and rel(alone[k], O.inv_root(a, 4, 1e-6)[0]) <= ia[k]["iters"] * 4 * 30 * 11.4 * 2.0 ** -24
+    assert rel(mixed[0], O.inv_root(big[0].astype(np.float64), 4, 1e-6)[0]) <= 1e-4
+    # zero iterations: 1 x 1, p = 1, Frobenius scaling: z A = 1 exactly
+    x, i = _roots(env, [np.array([[4.0]], np.float32)], p=1, eps=0.0, scaling=0, precision=B.PRECISION_FP32)
+    assert i[0]["iters"] == 0 and float(x[0][0, 0]) == 0.25
