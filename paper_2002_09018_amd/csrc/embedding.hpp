@@ -98,10 +98,32 @@ __global__ __launch_bounds__(kThreads) void emb_chunk_kernel(
   else emb_chunk_cols<false>(c, uniq, lens, offs, R, vals, feat, weight, dy, ld_dy, dim, vocab, nnz, U, part);
 }
 
-// One workgroup per potential run i: the row id (-1 past the active rows),
-// the counts (count[0] = active rows, count[1] = dropped entries), and for a
-// run that spans several chunks the sum of its chunk partials in chunk
-// order.  Rows of U at or past the active count are not written.
+// The row ids (-1 past the active rows), the counts (count[0] = active rows,
+// count[1] = dropped entries), and for every run that spans several chunks
+// the sum of its chunk partials in chunk order.  Workgroup b writes the ids
+// of kThreads runs and sums the run that starts in chunk b and reaches past
+// its end, if there is one (at most one per chunk, so about nnz / 64
+// workgroups; one workgroup per potential run took 117 us for 65536 lookups,
+// most of them to find nothing to do, and a Zipf head row's 110 partials were
+// added one load at a time).  Rows of U at or past the active count are not
+// written.
+template <bool VEC>
+__device__ __forceinline__ void emb_fix_cols(const float* __restrict__ part, int c0, int c1, bool first_slot1, int dim,
+                                             float* __restrict__ dst) {
+  constexpr int W = VEC ? 4 : 1;
+  for (int col = W * threadIdx.x; col < dim; col += W * kThreads) {
+    f4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int c = c0; c <= c1; ++c) {
+      const float* src = part + ((int64_t)c * 2 + (c == c0 && first_slot1 ? 1 : 0)) * dim + col;
+      if (VEC) acc += gload<f4v>(src);
+      else acc[0] += gload<float>(src);
+    }
+    if (VEC) gstore<f4v>(dst + col, acc);
+    else gstore<float>(dst + col, acc[0]);
+  }
+}
+
 __global__ __launch_bounds__(kThreads) void emb_fix_kernel(const int32_t* __restrict__ uniq,
                                                           const int32_t* __restrict__ lens,
                                                           const int32_t* __restrict__ offs,
@@ -109,28 +131,28 @@ __global__ __launch_bounds__(kThreads) void emb_fix_kernel(const int32_t* __rest
                                                           int nnz, const float* __restrict__ part,
                                                           int32_t* __restrict__ rows, float* __restrict__ U,
                                                           int32_t* __restrict__ count) {
-  const int i = blockIdx.x;
-  if (i >= nnz) return;
   const int R = *nruns;
   const bool tail_dropped = R > 0 && uniq[R - 1] == vocab;
-  if (i == 0 && threadIdx.x == 0) {
+  const int i0 = blockIdx.x * kThreads + threadIdx.x;
+  if (i0 == 0) {
     count[0] = R - (tail_dropped ? 1 : 0);
     count[1] = tail_dropped ? lens[R - 1] : 0;
   }
-  const bool active = i < R && uniq[i] != vocab;
-  if (threadIdx.x == 0) rows[i] = active ? uniq[i] : -1;
-  if (!active) return;
-  const int rs = offs[i], re = rs + lens[i];
-  const int c0 = rs / kEmbChunk, c1 = (re - 1) / kEmbChunk;
-  if (c0 == c1) return;  // summed in place by its chunk
-  for (int col = threadIdx.x; col < dim; col += kThreads) {
-    float acc = 0.f;
-    for (int c = c0; c <= c1; ++c) {
-      const int slot = (c == c0 && rs != c0 * kEmbChunk) ? 1 : 0;
-      acc += gload<float>(part + ((int64_t)c * 2 + slot) * dim + col);
-    }
-    gstore<float>(U + (int64_t)i * dim + col, acc);
+  if (i0 < nnz) rows[i0] = i0 < R && uniq[i0] != vocab ? uniq[i0] : -1;
+  const int c0 = blockIdx.x, t0 = c0 * kEmbChunk, t1 = t0 + kEmbChunk;
+  if (R < 1 || t1 >= nnz) return;  // nothing reaches past the last chunk
+  // the run holding entry t1 - 1
+  int lo = 0, hi = R - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (offs[mid] <= t1 - 1) lo = mid; else hi = mid - 1;
   }
+  const int rs = offs[lo], re = rs + lens[lo];
+  if (rs < t0 || re <= t1 || uniq[lo] == vocab) return;
+  float* dst = U + (int64_t)lo * dim;
+  const bool vec = (dim & 3) == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0;
+  if (vec) emb_fix_cols<true>(part, c0, (re - 1) / kEmbChunk, rs != t0, dim, dst);
+  else emb_fix_cols<false>(part, c0, (re - 1) / kEmbChunk, rs != t0, dim, dst);
 }
 
 // R = beta R + alpha * sum_s part[s] over all n elements, the partials added

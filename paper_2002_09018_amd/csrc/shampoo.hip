@@ -1756,7 +1756,7 @@ shampoo_status shampoo_embedding_rows(void* handle, const int32_t* idx, const in
                        vals_s, feat, weight, dy, ld_dy, dim, v32, nnz, U, cpart);
   }));
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_EMB, s, [&] {
-    hipLaunchKernelGGL(emb_fix_kernel, dim3(nnz), dim3(kThreads), 0, s, uniq, lens, offs, nruns, dim, v32, nnz,
+    hipLaunchKernelGGL(emb_fix_kernel, dim3(cdiv(nnz, kEmbChunk)), dim3(kThreads), 0, s, uniq, lens, offs, nruns, dim, v32, nnz,
                        (const float*)cpart, rows, U, count);
   }));
   return SHAMPOO_OK;
