@@ -128,7 +128,7 @@ __device__ __forceinline__ void epi_rows(const float* epi, float* dst, int64_t l
 // with gD set; a separate instantiation as well).
 // map: how workgroups find their tiles (kMapXcd, kMapDeal, kMapDiagLast).
 template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
-__global__ __launch_bounds__(kThreads, kMinWaves) void gemm_grouped_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_grouped_kernel(const GemmProblem* __restrict__ probs,
                                                                int nprob, int total_tiles, int map) {
   __shared__ __attribute__((aligned(16))) char smem[SplitShm<SA, SB>::bytes];
   // LIM: work depends on device-side counts and sits in the first logical

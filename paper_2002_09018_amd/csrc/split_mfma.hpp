@@ -70,11 +70,18 @@ template <>
 struct Planes<uint16_t> {
   static constexpr int n = 1;
 };
-// 16-deep steps per stage: bf16 x bf16 has one product per step, so its
-// stages are deeper (fewer barriers per product).
+// 16-deep steps per stage, and the waves per SIMD asked of the register
+// allocator.  bf16 x bf16 has one product per step and bf16 x fp32 three, so
+// their stages are two steps deep (fewer barriers per product: the mixed
+// update's G Rr, 444 GFLOP, 2.05 -> 1.6 ms).  Four steps for bf16 x bf16 leave
+// two workgroups to a compute unit and were slower (mixed bf16 statistics 1.56
+// against 1.29 ms): with one product per step the loads bound it, and more
+// workgroups hide them better.
 template <typename SA, typename SB>
 struct SplitSteps {
-  static constexpr int value = Planes<SA>::n + Planes<SB>::n == 2 ? 2 : 1;
+  static constexpr int np = Planes<SA>::n + Planes<SB>::n;
+  static constexpr int value = np == 6 ? 1 : 2;
+  static constexpr int waves = np == 2 ? 4 : kMinWaves;
 };
 
 // Global loads at element alignment (the typedefs' alignment would be lost
