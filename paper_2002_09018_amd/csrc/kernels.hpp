@@ -416,6 +416,7 @@ struct NewtonJob {
   double* part;     // per-tile partial sums (tiles_n^2 x 2)
   double* vec;      // MaxSV vector and partials ((2 tiles_n + 1) n)
   int n;
+  int slot;         // the caller's index of the job (info, warm_out)
   int tiles_n;      // ceil(n / 128)
   int up_begin;     // first logical upper-triangular tile
   int full_begin;   // first logical full-grid tile
@@ -958,7 +959,9 @@ __global__ __launch_bounds__(kThreads) void root_warm_update_kernel(RootState* _
 // End of the warm phase: records its outcome (warm_out, device int32
 // [njobs][2] = {outcome, warm iterations}, may be NULL) and hands the
 // matrices whose warm start was given up to the cold start.
-__global__ void root_warm_finish_kernel(RootState* __restrict__ st, int njobs, int32_t* __restrict__ warm_out) {
+template <typename T>
+__global__ void root_warm_finish_kernel(const NewtonJob<T>* __restrict__ jobs, RootState* __restrict__ st, int njobs,
+                                        int32_t* __restrict__ warm_out) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= njobs) return;
   RootState& s = st[j];
@@ -979,8 +982,8 @@ __global__ void root_warm_finish_kernel(RootState* __restrict__ st, int njobs, i
     s.warm_iters = s.iters;
   }
   if (warm_out) {
-    warm_out[2 * j] = s.warm;
-    warm_out[2 * j + 1] = s.warm_iters;
+    warm_out[2 * jobs[j].slot] = s.warm;
+    warm_out[2 * jobs[j].slot + 1] = s.warm_iters;
   }
 }
 
@@ -1883,7 +1886,7 @@ __global__ __launch_bounds__(64) void root_info_kernel(const NewtonJob<T>* __res
     }
   }
   if (lane != 0) return;
-  int32_t* io = reinterpret_cast<int32_t*>(info_out) + 8 * j;
+  int32_t* io = reinterpret_cast<int32_t*>(info_out) + 8 * jobs[j].slot;
   float* fo = reinterpret_cast<float*>(io);
   io[0] = s.status;
   io[1] = s.iters;

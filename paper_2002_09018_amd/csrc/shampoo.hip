@@ -268,11 +268,16 @@ template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename S
 shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t s, int cls) {
   if (probs.empty()) return SHAMPOO_OK;
   int total = 0, mixed = 0, sym = 1;
+  for (const auto& p : probs) mixed |= p.M != probs[0].M || p.N != probs[0].N || p.K != probs[0].K;
+  // Tiles with the longest contraction start first, so that a launch does
+  // not end on a few of them (each problem's result does not depend on its
+  // place in the launch).
+  if (mixed && !LIM)
+    std::stable_sort(probs.begin(), probs.end(), [](const GemmProblem& x, const GemmProblem& y) { return x.K > y.K; });
   for (auto& p : probs) {
     p.tiles_n = cdiv(p.N, kTile);
     p.tile_begin = total;
     total += p.sym ? p.tiles_n * (p.tiles_n + 1) / 2 : cdiv(p.M, kTile) * p.tiles_n;
-    mixed |= p.M != probs[0].M || p.N != probs[0].N || p.K != probs[0].K;
     sym &= p.sym;
   }
   // problems of different sizes: tiles dealt in chunks over the XCDs (grid
@@ -983,13 +988,13 @@ shampoo_status warm_phase(Handle* h, const NewtonJob<T>* djobs, const TileLists&
     }
   }
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
-    hipLaunchKernelGGL(root_warm_finish_kernel, dim3(cdiv(njobs, 64)), dim3(64), 0, s, st, njobs, warm_out);
+    hipLaunchKernelGGL(root_warm_finish_kernel<T>, dim3(cdiv(njobs, 64)), dim3(64), 0, s, djobs, st, njobs, warm_out);
   }));
   return SHAMPOO_OK;
 }
 
 template <typename T>
-std::vector<NewtonJob<T>> newton_table(const shampoo_root_job* jobs, int njobs, char* ws, const RootLayout& L,
+std::vector<NewtonJob<T>> newton_table(const shampoo_root_job* jobs, const int* slots, int njobs, char* ws, const RootLayout& L,
                                        int* total_up, int* total_full, int* total_flat) {
   std::vector<NewtonJob<T>> v(njobs);
   int up = 0, full = 0, flat = 0;
@@ -1018,6 +1023,7 @@ std::vector<NewtonJob<T>> newton_table(const shampoo_root_job* jobs, int njobs, 
       J.S[1] = reinterpret_cast<T*>(base + 5 * nn);
     }
     J.n = n;
+    J.slot = slots[j];
     J.tiles_n = cdiv(n, kTile);
     J.up_begin = up;
     J.full_begin = full;
@@ -1368,6 +1374,15 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     if (!jobs[j].A || !jobs[j].X) return fail(h, SHAMPOO_EINVAL, "job %d: A or X is NULL", j);
     if (jobs[j].A == jobs[j].X) return fail(h, SHAMPOO_EINVAL, "job %d: A and X alias", j);
   }
+  // Largest matrices first (states, tiles and tables in this order; results
+  // go to the caller's slots): the tiles of a launch that take longest then
+  // start first, and a launch of mixed sizes does not end on a few of them.
+  std::vector<int> order(njobs);
+  for (int j = 0; j < njobs; ++j) order[j] = j;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return jobs[x].n > jobs[y].n; });
+  std::vector<shampoo_root_job> sorted(njobs);
+  for (int j = 0; j < njobs; ++j) sorted[j] = jobs[order[j]];
+  jobs = sorted.data();
   const int prec = prm->precision;
   const RootLayout L = root_layout(jobs, njobs, prec);
   if (ws_bytes < L.total)
@@ -1381,13 +1396,13 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
   const NewtonJob<float>* j32 = nullptr;
   const NewtonJob<double>* j64 = nullptr;
   if (prec != SHAMPOO_PRECISION_FP64) {
-    auto t = newton_table<float>(jobs, njobs, ws, L, &up, &full, &flat);
+    auto t = newton_table<float>(jobs, order.data(), njobs, ws, L, &up, &full, &flat);
     const void* d = nullptr;
     STATUS_TRY(upload_table(h, t.data(), t.size() * sizeof(t[0]), s, &d));
     j32 = static_cast<const NewtonJob<float>*>(d);
   }
   if (prec != SHAMPOO_PRECISION_FP32) {
-    auto t = newton_table<double>(jobs, njobs, ws, L, &up, &full, &flat);
+    auto t = newton_table<double>(jobs, order.data(), njobs, ws, L, &up, &full, &flat);
     const void* d = nullptr;
     STATUS_TRY(upload_table(h, t.data(), t.size() * sizeof(t[0]), s, &d));
     j64 = static_cast<const NewtonJob<double>*>(d);
@@ -1441,19 +1456,11 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     tf.tcount = reinterpret_cast<int*>(ws + L.tcountf);
     tf.mixed = tl.mixed;
   }
-  // matrices whose whole fp32 iteration runs in one workgroup (largest first)
-  std::vector<int> small;
+  // matrices whose whole fp32 iteration runs in one workgroup: the last ones
+  int nsmall = 0;
   if (j32)
-    for (int j = 0; j < njobs; ++j)
-      if (jobs[j].n <= kSmallMax) small.push_back(j);
-  std::stable_sort(small.begin(), small.end(), [&](int x, int y) { return jobs[x].n > jobs[y].n; });
-  const bool all_small = (int)small.size() == njobs;
-  const int* dsmall = nullptr;
-  if (!small.empty()) {
-    const void* d = nullptr;
-    STATUS_TRY(upload_table(h, small.data(), small.size() * sizeof(int), s, &d));
-    dsmall = static_cast<const int*>(d);
-  }
+    while (nsmall < njobs && jobs[njobs - 1 - nsmall].n <= kSmallMax) ++nsmall;
+  const bool all_small = nsmall == njobs;
   const int nb1 = cdiv(njobs, 64);
   const int tail_all = prec == SHAMPOO_PRECISION_FP64 ? 1 : 0;
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
@@ -1574,7 +1581,7 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     int fails = -1;
     const bool cold = !(warm && warm_aborts == 0);
     if (!cold) fails = 0;  // every warm result was accepted: no cold start
-    if (cold && !small.empty()) {
+    if (cold && nsmall > 0) {
       SmallRootArgs q{};
       q.p = p;
       q.power = prm->scaling == SHAMPOO_SCALING_POWER4;
@@ -1585,8 +1592,7 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       q.tol = prm->tol;
       q.eps = eps;
       STATUS_TRY(launch(h, SHAMPOO_KCLASS_NEWTON_F32, s, [&] {
-        hipLaunchKernelGGL(newton_small_kernel, dim3((unsigned)small.size()), dim3(kSmallThreads), 0, s, j32, dsmall,
-                           st, q);
+        hipLaunchKernelGGL(newton_small_kernel, dim3(nsmall), dim3(kSmallThreads), 0, s, j32, njobs - nsmall, st, q);
       }));
     }
     if (cold && !all_small)

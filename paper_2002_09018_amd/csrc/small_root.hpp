@@ -421,15 +421,15 @@ struct SmallRoot {
   }
 };
 
-// One workgroup per listed job (list: job indices, n <= 128); jobs that are
-// not active (NOT_PD, sent to fp64 by the condition witness, kept from a warm
+// One workgroup per job from `first` on (n <= 128, largest first); jobs that
+// are not active (NOT_PD, sent to fp64 by the condition witness, kept from a warm
 // start) are left alone.  Waves past the matrix's blocks end at once (a
 // barrier counts the waves that are left).
 __global__ __launch_bounds__(kSmallThreads) void newton_small_kernel(const NewtonJob<float>* __restrict__ jobs,
-                                                                    const int* __restrict__ list,
+                                                                    int first,
                                                                     RootState* __restrict__ st, SmallRootArgs q) {
   __shared__ __attribute__((aligned(16))) char smem[kSmallShm];
-  const int j = list[blockIdx.x];
+  const int j = first + blockIdx.x;
   if (st[j].status != kActive) return;
   SmallRoot s;
   s.n = jobs[j].n;
