@@ -8,7 +8,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libshampoo.so")
 SOURCES = [os.path.join(HERE, "csrc", "shampoo.hip")]
 HEADERS = [os.path.join(HERE, "csrc", "kernels.hpp"), os.path.join(HERE, "csrc", "tile_mfma.hpp"), os.path.join(HERE, "csrc", "split_mfma.hpp"),
-           os.path.join(HERE, "csrc", "small_root.hpp"), os.path.join(HERE, "csrc", "embedding.hpp"),
+           os.path.join(HERE, "csrc", "small_root.hpp"), os.path.join(HERE, "csrc", "direct_mma.hpp"), os.path.join(HERE, "csrc", "embedding.hpp"),
            os.path.join(ROOT, "include", "shampoo.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

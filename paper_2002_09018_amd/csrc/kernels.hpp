@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "direct_mma.hpp"
 #include "split_mfma.hpp"
 #include "tile_mfma.hpp"
 
@@ -26,6 +27,11 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   for (int w = 0; w < kThreads / 64; ++w) s += red[w];
   return s;
 }
+
+// a x + b e, the product by a rounded first: one expression for every
+// epilogue, so an output does not depend on the path that stores it.
+__device__ __forceinline__ float affine(float a, float x, float b, float e) { return fmaf(b, e, a * x); }
+__device__ __forceinline__ double affine(double a, double x, double b, double e) { return fma(b, e, a * x); }
 
 template <typename SG>
 __device__ __forceinline__ float load_g(const void* G, int64_t i) {
@@ -120,6 +126,57 @@ __device__ __forceinline__ void epi_rows(const float* epi, float* dst, int64_t l
     const int idx = lane + 64 * k, rr = idx / kSeg, c4 = (idx % kSeg) * 4;
     gstore<f4v>(dst + (int64_t)rr * ld + c4, *reinterpret_cast<const f4v*>(epi + rr * kWaveTile + c4));
   }
+}
+
+// Graft pass 1 over a wave's 32 rows x 64 columns of P at (r0, c0), row by
+// row: D += G o G, and the squares of D^{-1/2} o G and of P added to smg and
+// sps.  get(idx, w) returns w values of P from element idx of the 32 x 64 on.
+// vec: the tile is full and every view allows 4-wide access.
+template <typename SGG, typename Get>
+__device__ __forceinline__ void graft_walk(const GemmProblem& P, int r0, int c0, int lane, bool vec, float& smg,
+                                           float& sps, Get&& get) {
+  constexpr int kRows = Mfma<float>::kM;
+  if (vec) {
+    constexpr int kSeg = kWaveTile / 4;
+#pragma unroll 1
+    for (int k = 0; k < kRows * kSeg / 64; ++k) {
+      const int idx = lane + 64 * k, rr = idx / kSeg, c4 = (idx % kSeg) * 4;
+      const f4v pv = get(rr * kWaveTile + c4, 4);
+      const int64_t gi = (int64_t)(r0 + rr) * P.ldg + c0 + c4;
+      float g[4];
+      G4<SGG>::load(P.gG, gi, g);
+      f4v d = gload<f4v>(P.gD + gi);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        d[e] += g[e] * g[e];
+        const float u = ada_dir(g[e], d[e]);
+        smg += u * u;
+        sps += pv[e] * pv[e];
+      }
+      gstore<f4v>(P.gD + gi, d);
+    }
+    return;
+  }
+#pragma unroll 1
+  for (int idx = lane; idx < kRows * kWaveTile; idx += 64) {
+    const int rr = idx / kWaveTile, cc = idx % kWaveTile;
+    const int r = r0 + rr, c = c0 + cc;
+    if (r >= P.M || c >= P.N) continue;
+    const float x = get(idx, 1)[0];
+    const int64_t gi = (int64_t)r * P.ldg + c;
+    const float g = load_g<SGG>(P.gG, gi);
+    const float d = gload<float>(P.gD + gi) + g * g;
+    gstore<float>(P.gD + gi, d);
+    const float u = ada_dir(g, d);
+    smg += u * u;
+    sps += x * x;
+  }
+}
+template <typename SGG>
+__device__ __forceinline__ bool graft_vec(const GemmProblem& P, int m0, int n0) {
+  return m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 && (P.ldg & 3) == 0 &&
+         (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 && (reinterpret_cast<uintptr_t>(P.gD) & 15) == 0 &&
+         (reinterpret_cast<uintptr_t>(P.gG) & (4 * sizeof(SGG) - 1)) == 0;
 }
 
 // LIM: honour the device-side limits kcount / mcount (a separate
@@ -217,9 +274,7 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
     {
       __shared__ double gred[kThreads / 64];
       float smg = 0.f, sps = 0.f;
-      const bool vec = m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 && (P.ldg & 3) == 0 &&
-                       (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 && (reinterpret_cast<uintptr_t>(P.gD) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(P.gG) & (4 * sizeof(SGG) - 1)) == 0;
+      const bool vec = graft_vec<SGG>(P, m0, n0);
       const bool rows16 = m0 + kTile <= P.M && n0 + kTile <= P.N && (P.ldc & 3) == 0 &&
                           (reinterpret_cast<uintptr_t>(P.C) & 15) == 0;
       // a block row of the wave's accumulators (64 columns at a time) goes
@@ -243,42 +298,18 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
             const int r = r0 + idx / kWaveTile, c = c0 + idx % kWaveTile;
             if (r < P.M && c < P.N) gstore<float>(P.C + (int64_t)r * P.ldc + c, epi[idx]);
           }
-        } else if (vec) {
-          constexpr int kSeg = kWaveTile / 4;
-#pragma unroll 1
-          for (int k = 0; k < F::kM * kSeg / 64; ++k) {
-            const int idx = lane + 64 * k, rr = idx / kSeg, c4 = (idx % kSeg) * 4;
-            const f4v pv = *reinterpret_cast<const f4v*>(epi + rr * kWaveTile + c4);
-            const int64_t gi = (int64_t)(r0 + rr) * P.ldg + c0 + c4;
-            gstore<f4v>(P.C + (int64_t)(r0 + rr) * P.ldc + c0 + c4, pv);
-            float g[4];
-            G4<SGG>::load(P.gG, gi, g);
-            f4v d = gload<f4v>(P.gD + gi);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              d[e] += g[e] * g[e];
-              const float u = ada_dir(g[e], d[e]);
-              smg += u * u;
-              sps += pv[e] * pv[e];
-            }
-            gstore<f4v>(P.gD + gi, d);
-          }
         } else {
-#pragma unroll 1
-          for (int idx = lane; idx < F::kM * kWaveTile; idx += 64) {
-            const int rr = idx / kWaveTile, cc = idx % kWaveTile;
-            const int r = r0 + rr, c = c0 + cc;
-            if (r >= P.M || c >= P.N) continue;
-            const float x = epi[rr * kWaveTile + cc];
-            gstore<float>(P.C + (int64_t)r * P.ldc + c, x);
-            const int64_t gi = (int64_t)r * P.ldg + c;
-            const float g = load_g<SGG>(P.gG, gi);
-            const float d = gload<float>(P.gD + gi) + g * g;
-            gstore<float>(P.gD + gi, d);
-            const float u = ada_dir(g, d);
-            smg += u * u;
-            sps += x * x;
-          }
+          graft_walk<SGG>(P, r0, c0, lane, vec, smg, sps, [&](int idx, int w) {
+            f4v x;
+            if (w == 4) {
+              x = *reinterpret_cast<const f4v*>(epi + idx);
+              gstore<f4v>(P.C + (int64_t)(r0 + idx / kWaveTile) * P.ldc + c0 + idx % kWaveTile, x);
+            } else {
+              x[0] = epi[idx];
+              gstore<float>(P.C + (int64_t)(r0 + idx / kWaveTile) * P.ldc + c0 + idx % kWaveTile, x[0]);
+            }
+            return x;
+          });
         }
       }
       if (graft) {
@@ -312,8 +343,7 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
           if (P.beta != 0.f) old = gload<f4>(P.C + (int64_t)c * P.ldc + r);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            float x = P.alpha * acc.c[i][j][4 * g + q];
-            if (P.beta != 0.f) x += P.beta * old[q];
+            const float x = affine(P.alpha, acc.c[i][j][4 * g + q], P.beta, old[q]);
             gstore<float>(P.C + (int64_t)(r + q) * P.ldc + c, x);
             w[q] = x;
           }
@@ -337,8 +367,8 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
         for (int v = 0; v < F::kAcc; ++v) {
           const int r = wm0 + i * F::kM + F::row(lane, v);
           const int c = c0 + j * F::kM + F::col(lane);
-          float x = P.alpha * acc.c[i][j][v];
-          if (P.beta != 0.f) x += P.beta * gload<float>(P.C + (int64_t)r * P.ldc + c);
+          const float x =
+              affine(P.alpha, acc.c[i][j][v], P.beta, P.beta != 0.f ? gload<float>(P.C + (int64_t)r * P.ldc + c) : 0.f);
           epi[F::row(lane, v) * kWaveTile + j * F::kM + F::col(lane)] = x;
         }
       epi_rows(epi, P.C + (int64_t)(wm0 + i * F::kM) * P.ldc + c0, P.ldc, lane);
@@ -357,11 +387,79 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
         if (helper && i < NB / 2) continue;
         if (r >= P.M || c >= P.N) continue;
         if (diag && r > c) continue;
-        float x = P.alpha * acc.c[i][j][v];
-        if (P.beta != 0.f) x += P.beta * gload<float>(P.C + (int64_t)r * P.ldc + c);
+        const float x =
+            affine(P.alpha, acc.c[i][j][v], P.beta, P.beta != 0.f ? gload<float>(P.C + (int64_t)r * P.ldc + c) : 0.f);
         gstore<float>(P.C + (int64_t)r * P.ldc + c, x);
         if (P.sym && r != c) gstore<float>(P.C + (int64_t)c * P.ldc + r, x);
       }
+}
+
+// The same products for launches of few tiles, one wave per 32 x 32 block
+// (direct_mma.hpp): workgroup b is block b & 15 of logical tile b >> 4.
+// Plain and symmetric outputs; a graft problem's P only (graft_tile_kernel
+// follows).
+template <typename SA, int LA, typename SB, int LB>
+__global__ __launch_bounds__(64) void gemm_direct_kernel(const GemmProblem* __restrict__ probs, int nprob) {
+  const int t = blockIdx.x >> 4;
+  const GemmProblem P = probs[find_problem_gemm(probs, nprob, t)];
+  int ti, tj, bi, bj;
+  const int lt = t - P.tile_begin;
+  if (P.sym) unrank_upper(lt, P.tiles_n, ti, tj);
+  else {
+    const int tm = (P.M + kTile - 1) / kTile;
+    tj = lt / tm;
+    ti = lt - tj * tm;
+  }
+  sub_block(blockIdx.x & 15, bi, bj);
+  const int m0 = ti * kTile + bi, n0 = tj * kTile + bj;
+  if (m0 >= P.M || n0 >= P.N || (P.sym && m0 > n0)) return;
+  Operand<SA> A{reinterpret_cast<const SA*>(P.A), P.lda, P.a_rows, P.a_cols};
+  Operand<SB> B{reinterpret_cast<const SB*>(P.B), P.ldb, P.b_rows, P.b_cols};
+  const block_acc acc = direct_mma<true, SA, LA, SB, LB>(A, B, m0, n0, P.K);
+  typedef Mfma<float> F;
+  const int lane = threadIdx.x, c = n0 + F::col(lane);
+  if (c >= P.N) return;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int r = m0 + F::row(lane, v);
+    if (r >= P.M || (P.sym && r > c)) continue;
+    float* d = P.C + (int64_t)r * P.ldc + c;
+    const float x = affine(P.alpha, acc[v], P.beta, P.beta != 0.f ? gload<float>(d) : 0.f);
+    gstore<float>(d, x);
+    if (P.sym && r != c) gstore<float>(P.C + (int64_t)c * P.ldc + r, x);
+  }
+}
+
+// Graft pass 1 of the problems a gemm_direct_kernel launch wrote: per 128 x
+// 128 tile, in the order (and with the partials) of the fused epilogue.
+template <typename SGG>
+__global__ __launch_bounds__(kThreads) void graft_tile_kernel(const GemmProblem* __restrict__ probs, int nprob) {
+  __shared__ double gred[kThreads / 64];
+  const int t = blockIdx.x;
+  const GemmProblem P = probs[find_problem_gemm(probs, nprob, t)];
+  if (!P.gD) return;
+  const int lt = t - P.tile_begin, tm = (P.M + kTile - 1) / kTile;
+  const int m0 = (lt % tm) * kTile, n0 = (lt / tm) * kTile;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool vec = graft_vec<SGG>(P, m0, n0);
+  float smg = 0.f, sps = 0.f;
+#pragma unroll 1
+  for (int i = 0; i < 2; ++i) {
+    const int r0 = m0 + (wave >> 1) * kWaveTile + 32 * i, c0 = n0 + (wave & 1) * kWaveTile;
+    graft_walk<SGG>(P, r0, c0, lane, vec, smg, sps, [&](int idx, int w) {
+      const float* src = P.C + (int64_t)(r0 + idx / kWaveTile) * P.ldc + c0 + idx % kWaveTile;
+      f4v x;
+      if (w == 4) x = gload<f4v>(src);
+      else x[0] = gload<float>(src);
+      return x;
+    });
+  }
+  const double a = block_sum((double)smg, gred);
+  const double b = block_sum((double)sps, gred);
+  if (threadIdx.x == 0) {
+    P.gpart[2 * (P.part_base + lt) + 0] = a;
+    P.gpart[2 * (P.part_base + lt) + 1] = b;
+  }
 }
 
 // ============================================================================
@@ -683,8 +781,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
   RootProduct<T, L, L>::run(acc, A, B, m0, n0, n, smem, ti == tj);
   // value of output element (r, c) from its accumulator
   auto fin = [&](T v, int r, int c) -> T {
-    T x = ca * v;
-    if (pe) x += cb * gload<T>(pe + (int64_t)r * n + c);
+    T x = affine(ca, v, cb, pe ? gload<T>(pe + (int64_t)r * n + c) : (T)0);
     if (r == c) x += cg;
     return x;
   };
@@ -725,7 +822,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
           if (pe) e4 = gload<f4>(reinterpret_cast<const float*>(pe) + (int64_t)c * n + r);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            T x = ca * acc.c[i][jj][4 * g + q] + cb * (T)e4[q];
+            T x = affine(ca, acc.c[i][jj][4 * g + q], cb, (T)e4[q]);
             if (r + q == c) x += cg;
             w[q] = (float)x;
             gstore<T>(pc + (int64_t)(r + q) * n + c, x);
@@ -752,6 +849,63 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
           if (r != c) gstore<T>(pc + (int64_t)c * n + r, x);
           track(x, r, c);
         }
+  }
+  if (resid) {
+    rmax = wave_max(rmax);
+    if (lane == 0 && rmax > 0.f) atomicMax(&st[j].resid_bits, __float_as_uint(rmax));
+  }
+}
+
+// newton_stage_kernel<float> for launches of few tiles, one wave per 32 x 32
+// block (direct_mma.hpp): workgroup b is block b & 15 of work item b >> 4 (the
+// products of one tile follow each other).
+__global__ __launch_bounds__(64) void newton_direct_kernel(const NewtonJob<float>* __restrict__ jobs,
+                                                           const uint32_t* __restrict__ tlist,
+                                                           const int* __restrict__ tcount,
+                                                           RootState* __restrict__ st, NewtonStage S) {
+  const int np = S.nprod, l = blockIdx.x >> 4;
+  if (l >= np * tcount[0]) return;
+  const int t = l / np, prod = l - t * np;
+  const uint32_t code = tlist[t];
+  const int j = (int)(code >> 10);
+  int bi, bj;
+  sub_block(blockIdx.x & 15, bi, bj);
+  const int m0 = (int)((code >> 5) & 31) * kTile + bi, n0 = (int)(code & 31) * kTile + bj;
+  if (st[j].status != kActive) return;
+  const NewtonJob<float>* J = jobs + j;
+  const int n = J->n;
+  if (m0 >= n || n0 >= n || m0 > n0) return;
+  const int par = st[j].parity;
+  const int ie = pick3(prod, S.q[0].e, S.q[1].e, S.q[2].e);
+  const bool resid = pick3(prod, S.q[0].resid, S.q[1].resid, S.q[2].resid) != 0;
+  const float ca = (float)pick3(prod, S.q[0].ca, S.q[1].ca, S.q[2].ca);
+  const float cb = (float)pick3(prod, S.q[0].cb, S.q[1].cb, S.q[2].cb);
+  const float cg = (float)pick3(prod, S.q[0].cg, S.q[1].cg, S.q[2].cg);
+  const float* pa = newton_buf(J, par, pick3(prod, S.q[0].a, S.q[1].a, S.q[2].a));
+  const float* pb = newton_buf(J, par, pick3(prod, S.q[0].b, S.q[1].b, S.q[2].b));
+  float* pc = newton_buf(J, par, pick3(prod, S.q[0].dst, S.q[1].dst, S.q[2].dst));
+  const float* pe = ie >= 0 ? newton_buf(J, par, ie) : nullptr;
+  Operand<float> A{pa, n, n, n};
+  Operand<float> B{pb, n, n, n};
+  const block_acc acc = direct_mma<false, float, kLayoutRow, float, kLayoutRow>(A, B, m0, n0, n);
+  typedef Mfma<float> F;
+  const int lane = threadIdx.x, c = n0 + F::col(lane);
+  float rmax = 0.f;
+  if (c < n) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = m0 + F::row(lane, v);
+      if (r >= n || r > c) continue;
+      float x = affine(ca, acc[v], cb, pe ? gload<float>(pe + (int64_t)r * n + c) : 0.f);
+      if (r == c) x += cg;
+      gstore<float>(pc + (int64_t)r * n + c, x);
+      if (r != c) gstore<float>(pc + (int64_t)c * n + r, x);
+      if (resid) {
+        float d = (float)fabs((double)x - (r == c ? 1.0 : 0.0));
+        if (!(d <= 3.0e38f)) d = INFINITY;  // NaN or overflow
+        rmax = rmax > d ? rmax : d;
+      }
+    }
   }
   if (resid) {
     rmax = wave_max(rmax);

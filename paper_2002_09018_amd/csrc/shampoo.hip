@@ -264,6 +264,19 @@ constexpr int kDiagLastMaxPerXcd = 128;
 // share the slabs of G they read in L2.
 constexpr int kDiagLastMinK = 2048;
 
+// Launches of at most this many 128 x 128 tiles take the one-wave-per-block
+// form (direct_mma.hpp; results are the same bits).  Measured, tiles per
+// launch: time with 128 x 128 workgroups -> direct.
+//   Statistics call (two launches): 1: 48 -> 25 us (128 x 128); 40: 88 -> 60
+//   us (512 x 512); 72: 166 -> 152 us (1024 x 1024); 80: 89 -> 98 us (512 x
+//   512); 96: 63 -> 71 us (256 x 256).
+//   Root call (products of 1 or 2 times the tiles): 3: 489 -> 329 us (256 x
+//   256); 72: 1037 -> 860 us (1024 x 1024); 80: 682 -> 586 us, and 627 us with
+//   its two-product stages (160 tiles) direct as well (512 x 512); 96: 543 ->
+//   485 us (256 x 256).
+constexpr int kDirectTiles = 72;
+constexpr int kDirectRootTiles = 96;
+
 template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
 shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t s, int cls) {
   if (probs.empty()) return SHAMPOO_OK;
@@ -292,6 +305,22 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
                                          : total;
   const void* d = nullptr;
   STATUS_TRY(upload_table(h, probs.data(), probs.size() * sizeof(GemmProblem), s, &d));
+  if constexpr (!LIM) {
+    if (total <= kDirectTiles) {
+      const int np = (int)probs.size();
+      return launch(h, cls, s, [&] {
+        hipLaunchKernelGGL((gemm_direct_kernel<SA, LA, SB, LB>), dim3(16 * total), dim3(64), 0, s,
+                           (const GemmProblem*)d, np);
+        if constexpr (!std::is_same<SGG, void>::value) {
+          for (const auto& p : probs)
+            if (p.gD) {
+              hipLaunchKernelGGL(graft_tile_kernel<SGG>, dim3(total), dim3(kThreads), 0, s, (const GemmProblem*)d, np);
+              break;
+            }
+        }
+      });
+    }
+  }
   auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG>;
   const int lds = 0;  // static LDS
   const int np = (int)probs.size();
@@ -796,15 +825,25 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
   // fails_out: set to the number of matrices stopped unaccepted (MAXITER,
   // DIVERGED) when the polled counts showed that every matrix stopped; left
   // untouched otherwise.
-  const int lds = 0;  // static LDS
-  auto kstage = newton_stage_kernel<T>;
+  // one launch of a stage's products over the tiles of the active matrices
+  auto run_stage = [&](const NewtonStage& S) {
+    if constexpr (sizeof(T) == 4) {
+      if (S.nprod * total_up <= kDirectRootTiles)
+        return launch(h, cls, s, [&] {
+          hipLaunchKernelGGL(newton_direct_kernel, dim3(16 * S.nprod * total_up), dim3(64), 0, s, djobs, tl.tlist,
+                             tl.tcount, st, S);
+        });
+    }
+    // (padded for the chunked deal of matrices of different sizes)
+    const int work = S.nprod * total_up;
+    const int grid = tl.mixed ? cdiv(work, 8 * kDealChunk) * 8 * kDealChunk : 8 * (cdiv(work, 8) + 1);
+    return launch(h, cls, s, [&] {
+      hipLaunchKernelGGL(newton_stage_kernel<T>, dim3(grid), dim3(kThreads), 0, s, djobs, tl.tlist, tl.tcount, njobs,
+                         st, S, tl.mixed);
+    });
+  };
   const bool power = scaling == SHAMPOO_SCALING_POWER4;
   const int nb1 = cdiv(njobs, 64);
-  // grid of a product launch of np products per tile (padded for the
-  // chunked deal of matrices of different sizes)
-  auto pgrid = [&](int np) {
-    return tl.mixed ? cdiv(np * total_up, 8 * kDealChunk) * 8 * kDealChunk : 8 * (cdiv(np * total_up, 8) + 1);
-  };
   // M0 (and, with the Frobenius scaling, X1 and the residual of M0); the
   // tiles of the matrices that take part in this phase
   STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
@@ -825,12 +864,8 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
     sq0.nprod = sq1.nprod = 1;
     sq0.q[0] = make_prod(kBufMc, kBufMc, kBufNone, kBufS0, 1.0, 0.0, 0.0, 0);
     sq1.q[0] = make_prod(kBufS0, kBufS0, kBufNone, kBufS1, 1.0, 0.0, 0.0, 0);
-    for (const NewtonStage* S : {&sq0, &sq1}) {
-      STATUS_TRY(launch(h, cls, s, [&] {
-        hipLaunchKernelGGL(kstage, dim3(pgrid(1)), dim3(kThreads), lds, s, djobs, tl.tlist, tl.tcount, njobs, st, *S,
-                           tl.mixed);
-      }));
-    }
+    STATUS_TRY(run_stage(sq0));
+    STATUS_TRY(run_stage(sq1));
     const double a = 1.25, b = -0.25;
     STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
       hipLaunchKernelGGL(frob_s1_kernel<T>, dim3(total_up), dim3(kThreads), 0, s, djobs, njobs, st, total_up);
@@ -859,10 +894,7 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
         NewtonStage f{};
         f.nprod = 1;
         f.q[0] = make_prod(kBufMc, kBufS1, kBufS0, kBufMn, 1.0, 1.0, 0.0, 1);
-        STATUS_TRY(launch(h, cls, s, [&] {
-          hipLaunchKernelGGL(kstage, dim3(pgrid(1)), dim3(kThreads), lds, s, djobs, tl.tlist, tl.tcount, njobs, st, f,
-                             tl.mixed);
-        }));
+        STATUS_TRY(run_stage(f));
         break;  // the iteration's remaining stages are folded into this product
       }
       if (power && it == 0 && q == 0) {
@@ -873,10 +905,7 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
         }));
         continue;
       }
-      STATUS_TRY(launch(h, cls, s, [&] {
-        hipLaunchKernelGGL(kstage, dim3(pgrid(S.nprod)), dim3(kThreads), lds, s, djobs, tl.tlist, tl.tcount, njobs,
-                           st, S, tl.mixed);
-      }));
+      STATUS_TRY(run_stage(S));
     }
     const int ring = 2 * (it % kCountRing);
     int* slot = dcount + ring;

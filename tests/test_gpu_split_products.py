@@ -130,3 +130,47 @@ def test_non_finite(env, m, n):
         f = np.isfinite(want)
         share = float((np.abs(got[f] - want[f]) / (1e-5 * np.abs(want[f]))).max())
         assert share <= 1.0, share
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("m,n,pad", [(1, 1, 0), (33, 31, 1), (128, 128, 0), (129, 300, 3), (257, 64, 0), (300, 520, 0)])
+def test_few_tiles_same_bits(env, m, n, pad, bf16):
+    """A block alone (few tiles: one wave per 32 x 32 block) and the same
+    block in a launch of many tiles (128 x 128 workgroups): statistics,
+    preconditioning and the fused graft agree bit for bit, with a non-finite
+    gradient entry in one of the statistics."""
+    torch, B, dev, h = env
+    dt = torch.bfloat16 if bf16 else torch.float32
+    r = np.random.default_rng(100 * m + n)
+    g = r.standard_normal((m, n)).astype(np.float32)
+    l, q = (to_dev(torch, (0.5 * (a + a.T)).astype(np.float32), dev)
+            for a in (r.standard_normal((m, m)), r.standard_normal((n, n))))
+
+    def block(left, right, x):
+        t = dict(G=_view(torch, dev, x, pad, pad, dt))
+        for k, v in (("W", 1.0), ("D", 0.5), ("P", 0.0)):
+            t[k] = _view(torch, dev, np.full((m, n), v, np.float32), pad, 0, torch.float32)
+        return B.Block(L=torch.ones(m, m, device=dev), R=torch.ones(n, n, device=dev), Lr=l if left else None,
+                       Rr=q if right else None, **t)
+
+    big = torch.zeros(1024, 1536, device=dev, dtype=dt)
+    eye, eyn = torch.eye(1024, device=dev), torch.eye(1536, device=dev)
+    say(f"few tiles {m}x{n} pad={pad} bf16={bf16}")
+    for left, right in ((True, True), (True, False), (False, True)):
+        x = g.copy()
+        x[m // 2, n // 3] = np.inf if left and right else 0.25
+        fill = B.Block(G=big, W=torch.zeros(1024, 1536, device=dev), D=torch.zeros(1024, 1536, device=dev),
+                       P=torch.zeros(1024, 1536, device=dev), L=torch.zeros(1024, 1024, device=dev),
+                       R=torch.zeros(1536, 1536, device=dev), Lr=eye if left else None, Rr=eyn if right else None)
+        got = []
+        for extra in ([], [fill]):
+            b = block(left, right, x)
+            norms = torch.zeros(3 * (1 + len(extra)), device=dev)
+            B.shampoo_update_stats(h, [b] + extra, beta2=0.9)
+            b.G[m // 2, n // 3] = 0.25
+            B.shampoo_precondition_graft(h, [b] + extra, 0.05, norms=norms)
+            torch.cuda.synchronize()
+            got.append([host(v.contiguous()) for v in (b.L, b.R, b.P, b.D, b.W, norms[:3])])
+        for a, c, what in zip(*got, ("L", "R", "P", "D", "W", "norms")):
+            f = np.isfinite(a)
+            assert np.array_equal(f, np.isfinite(c)) and np.array_equal(a[f], c[f]), (what, left, right)
