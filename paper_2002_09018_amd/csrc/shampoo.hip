@@ -78,7 +78,14 @@ struct TableEntry {
   hipEvent_t ev = nullptr;
   uint64_t last = 0;
   bool used = false;
+  bool own = false;  // dev and host are allocations of this entry (else its slab slot)
 };
+// Cached tables per handle, and the bytes of an entry's slot in the handle's
+// slabs (larger tables are allocated).  A step over one of a few gradient
+// buffers uses about six tables: 64 entries were replaced in turn by a
+// program cycling 16 buffers, a copy before every launch.
+constexpr int kTableEntries = 256;
+constexpr size_t kTableSlot = 4096;
 
 struct TimedLaunch {
   int cls;
@@ -89,6 +96,8 @@ struct Handle {
   int device = 0;
   std::string err;
   std::vector<TableEntry> cache;
+  char* slab_dev = nullptr;  // kTableEntries slots each, allocated with the first table
+  char* slab_host = nullptr;
   std::vector<int> pending;  // cache entries referenced by the launches being enqueued
   uint64_t clock = 0;
   void* zbuf = nullptr;  // intermediate G Rr of two-sided preconditioning (grown on demand)
@@ -162,9 +171,15 @@ shampoo_status upload_table(Handle* h, const void* data, size_t bytes, hipStream
     }
   }
   int slot = -1;
-  if (h->cache.size() < 64) {
+  if (!h->slab_dev) HIP_TRY(h, hipMalloc(reinterpret_cast<void**>(&h->slab_dev), kTableEntries * kTableSlot));
+  if (!h->slab_host)
+    HIP_TRY(h, hipHostMalloc(reinterpret_cast<void**>(&h->slab_host), kTableEntries * kTableSlot, hipHostMallocDefault));
+  if (h->cache.size() < (size_t)kTableEntries) {
     h->cache.emplace_back();
     slot = (int)h->cache.size() - 1;
+    h->cache[slot].dev = h->slab_dev + slot * kTableSlot;
+    h->cache[slot].host = h->slab_host + slot * kTableSlot;
+    h->cache[slot].cap = kTableSlot;
     HIP_TRY(h, hipEventCreateWithFlags(&h->cache[slot].ev, hipEventDisableTiming));
   } else {
     uint64_t best = UINT64_MAX;
@@ -174,10 +189,13 @@ shampoo_status upload_table(Handle* h, const void* data, size_t bytes, hipStream
   }
   TableEntry& e = h->cache[slot];
   if (e.cap < bytes) {
-    if (e.dev) HIP_TRY(h, hipFree(e.dev));
-    if (e.host) HIP_TRY(h, hipHostFree(e.host));
+    e.used = false;
+    e.cap = 0;
+    if (e.own && e.dev) HIP_TRY(h, hipFree(e.dev));
+    if (e.own && e.host) HIP_TRY(h, hipHostFree(e.host));
     e.dev = e.host = nullptr;
-    const size_t cap = std::max<size_t>(align256(bytes), 4096);
+    e.own = true;
+    const size_t cap = align256(bytes);
     HIP_TRY(h, hipMalloc(&e.dev, cap));
     HIP_TRY(h, hipHostMalloc(&e.host, cap, hipHostMallocDefault));
     e.cap = cap;
@@ -682,10 +700,17 @@ RootLayout root_layout(const shampoo_root_job* jobs, int njobs, int precision) {
   return L;
 }
 
+// One step of the scalar recurrence m <- ((p + 1 - m) / p)^p m.
+inline double scalar_step(double m, int p) {
+  const double f = (p + 1.0 - m) / p;
+  for (int q = 0; q < p; ++q) m *= f;
+  return m;
+}
+
 int host_scalar_iters(double m, int p, double tol, int cap) {
   int k = 0;
   while (fabs(m - 1.0) > tol && k < cap) {
-    m = pow((p + 1.0 - m) / p, p) * m;
+    m = scalar_step(m, p);
     ++k;
   }
   return k;
@@ -907,14 +932,14 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
       }
       STATUS_TRY(run_stage(S));
     }
+    // with polling, the counts go straight to pinned host memory
     const int ring = 2 * (it % kCountRing);
-    int* slot = dcount + ring;
+    int* slot = poll ? h->pinned + ring : dcount + ring;
     STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
       hipLaunchKernelGGL(root_update_kernel, dim3(1), dim3(kThreads), 0, s, st, njobs, 0, tol, cap, slot, esc_thr,
                          esc_n, tl.tmap, tl.ubegin, tl.diag_last, tl.tlist, tl.tcount);
     }));
     if (poll) {
-      HIP_TRY(h, hipMemcpyAsync(h->pinned + ring, slot, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
       HIP_TRY(h, hipEventRecord(h->poll_ev[it & 1], s));
       if (it >= 1) {
         HIP_TRY(h, hipEventSynchronize(h->poll_ev[(it - 1) & 1]));
@@ -997,14 +1022,14 @@ shampoo_status warm_phase(Handle* h, const NewtonJob<T>* djobs, const TileLists&
     for (const NewtonStage& S : stages) STATUS_TRY(run(S));
     STATUS_TRY(run(xm));
     STATUS_TRY(run(comm));
+    // with polling, the counts go straight to pinned host memory
     const int ring = 2 * (it % kCountRing);
-    int* slot = dcount + ring;
+    int* slot = poll ? h->pinned + ring : dcount + ring;
     STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
       hipLaunchKernelGGL(root_warm_update_kernel, dim3(1), dim3(kThreads), 0, s, st, njobs, 0, tol, comm_tol, cap,
                          slot, tf.tmap, tf.ubegin, tf.tlist, tf.tcount);
     }));
     if (poll) {
-      HIP_TRY(h, hipMemcpyAsync(h->pinned + ring, slot, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
       HIP_TRY(h, hipEventRecord(h->poll_ev[it & 1], s));
       if (it >= 1) {
         HIP_TRY(h, hipEventSynchronize(h->poll_ev[(it - 1) & 1]));
@@ -1216,10 +1241,12 @@ shampoo_status shampoo_destroy(void* handle) {
   DeviceGuard g(h->device);
   (void)hipDeviceSynchronize();
   for (auto& e : h->cache) {
-    if (e.dev) (void)hipFree(e.dev);
-    if (e.host) (void)hipHostFree(e.host);
+    if (e.own && e.dev) (void)hipFree(e.dev);
+    if (e.own && e.host) (void)hipHostFree(e.host);
     if (e.ev) (void)hipEventDestroy(e.ev);
   }
+  if (h->slab_dev) (void)hipFree(h->slab_dev);
+  if (h->slab_host) (void)hipHostFree(h->slab_host);
   for (auto& t : h->timed) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
@@ -1546,8 +1573,8 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     const int k32 = host_scalar_iters(m0, p, tl, 1000) + 1;
     cap32 = std::min(cap32, std::max(k32, 1));
     double lo = 1e-300, hi = 1.0;
-    for (int b = 0; b < 200; ++b) {
-      const double mid = sqrt(lo * hi);
+    while (hi > lo * (1.0 + 1e-13)) {
+      const double mid = sqrt(lo) * sqrt(hi);
       if (host_scalar_iters(mid, p, tl, cap32 + 1) <= cap32) hi = mid; else lo = mid;
     }
     m1 = hi;
@@ -1599,7 +1626,7 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       std::vector<float> thr(cap);
       double m = m1;
       for (int k = 0; k < cap; ++k) {
-        m = pow((p + 1.0 - m) / p, p) * m;
+        m = scalar_step(m, p);
         thr[k] = (float)(1.0 - m);  // escalating a borderline matrix early is harmless
       }
       const void* d = nullptr;
@@ -1628,7 +1655,7 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       STATUS_TRY(newton_phase<float>(h, j32, tl, njobs, st, dcount, up, full, flat, prog, p, prm->scaling, prm->tol,
                                      cap, prm->poll, SHAMPOO_KCLASS_NEWTON_F32, esc, esc_n, s, &fails));
     if (prec == SHAMPOO_PRECISION_AUTO) {
-      int* esc_count = dcount + 2 * kCountRing + 2;
+      int* esc_count = (prm->poll ? h->pinned : dcount) + 2 * kCountRing + 2;
       STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
         hipLaunchKernelGGL(root_escalate_kernel, dim3(1), dim3(kThreads), 0, s, st, njobs, esc_count);
       }));
@@ -1639,8 +1666,8 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       } else {
         // no polled count: the phase ended at its cap with matrices still
         // running, or every matrix was small
-        HIP_TRY(h, hipMemcpyAsync(h->pinned + 2 * kCountRing + 2, esc_count, sizeof(int), hipMemcpyDeviceToHost, s));
-        HIP_TRY(h, hipStreamSynchronize(s));
+        HIP_TRY(h, hipEventRecord(h->poll_ev[0], s));
+        HIP_TRY(h, hipEventSynchronize(h->poll_ev[0]));
         run64 = h->pinned[2 * kCountRing + 2] > 0;
       }
     }
