@@ -483,7 +483,7 @@ struct RootState {
   float resid;       // residual after the last iteration
   int escalate;      // AUTO policy: redo in fp64
   int precision;     // 32 or 64: phase that produced the result
-  int sv_done;       // MaxSV stopped
+  int sv_done;       // MaxSV stopped; in the Lanczos iteration the last test's verdict (kLz...)
   int sv_steps;      // MaxSV power steps taken
   int lz_done;       // Lanczos condition witness stopped (AUTO pre-escalation)
   int lz_steps;      // Lanczos steps taken
@@ -1234,6 +1234,124 @@ __global__ void root_warm_finish_kernel(const NewtonJob<T>* __restrict__ jobs, R
 }
 
 // ---------------------------------------------------------------------------
+// The witness test of the Lanczos iteration (lanczos_init_kernel tells what it
+// is for) after lz_steps steps; mthr: m1 of the fp32 cap.  The caller is one
+// workgroup of kThreads.
+// ---------------------------------------------------------------------------
+constexpr int kLanczosMax = 96;
+enum : int { kLzOpen = 0, kLzStop = 1, kLzShown = 2 };  // take the fp32 phase; go straight to fp64
+constexpr int kSturmPoints = 4;  // points of a thread: 1024 of a workgroup per round
+
+// *below[q] = whether the symmetric tridiagonal (a[0..m), off-diagonal squares
+// b2[0..m-1)) has an eigenvalue below x[q]: a negative pivot of the LDL^T
+// factorisation of T - x I (Sturm).  Four independent chains of divisions per
+// thread fill each other's latency.
+__device__ inline void sturm_below(const double* a, const double* b2, int m, const double* x, bool* below) {
+  double d[kSturmPoints];
+#pragma unroll
+  for (int q = 0; q < kSturmPoints; ++q) {
+    d[q] = 1.0;
+    below[q] = false;
+  }
+  for (int i = 0; i < m; ++i) {
+    const double ai = a[i], bi = i > 0 ? b2[i - 1] : 0.0;
+#pragma unroll
+    for (int q = 0; q < kSturmPoints; ++q) {
+      d[q] = ai - x[q] - bi / d[q];
+      if (d[q] == 0.0) d[q] = -1e-300;  // an exact zero pivot counts as negative
+      below[q] |= d[q] < 0.0;
+    }
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void lanczos_test(const NewtonJob<T>* __restrict__ jobs, int j, RootState* __restrict__ st,
+                                             int p, double mthr) {
+  __shared__ double sa[kLanczosMax], sb[kLanczosMax], sb2[kLanczosMax];
+  __shared__ double slo, shi;
+  __shared__ int sfirst;
+  constexpr int kPoints = kSturmPoints * kThreads;
+  const int m = st[j].lz_steps;
+  if (st[j].status != kActive || st[j].lz_done || st[j].sv_done != kLzOpen || m == 0) return;
+  const NewtonJob<T>* J = jobs + j;
+  const int n = J->n;
+  const double* al = J->vec + n + 2 * (int64_t)J->tiles_n * n + n;
+  const double* be = al + kLanczosMax;
+  for (int i = threadIdx.x; i < m; i += kThreads) {
+    sa[i] = al[i];
+    sb[i] = be[i];
+    sb2[i] = be[i] * be[i];
+  }
+  __syncthreads();
+  // smallest Ritz value: the Gershgorin interval, narrowed by three rounds of
+  // multisection (every thread looks for eigenvalues below its own points)
+  if (threadIdx.x < 64) {
+    double lo = INFINITY, hi = -INFINITY;
+    for (int i = threadIdx.x; i < m; i += 64) {
+      const double r = (i > 0 ? fabs(sb[i - 1]) : 0.0) + (i + 1 < m ? fabs(sb[i]) : 0.0);
+      lo = fmin(lo, sa[i] - r);
+      hi = fmax(hi, sa[i] + r);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, off));
+      hi = fmax(hi, __shfl_xor(hi, off));
+    }
+    if (threadIdx.x == 0) {
+      slo = lo;
+      shi = hi;
+    }
+  }
+  for (int round = 0; round < 3; ++round) {
+    if (threadIdx.x == 0) sfirst = kPoints;
+    __syncthreads();
+    const double lo = slo, w = (shi - slo) / kPoints;
+    double x[kSturmPoints];
+    bool below[kSturmPoints];
+#pragma unroll
+    for (int q = 0; q < kSturmPoints; ++q) x[q] = lo + w * (q * kThreads + (int)threadIdx.x + 1);
+    sturm_below(sa, sb2, m, x, below);
+    int first = kPoints;
+#pragma unroll
+    for (int q = kSturmPoints - 1; q >= 0; --q)
+      if (below[q]) first = q * kThreads + (int)threadIdx.x;
+    if (first < kPoints) atomicMin(&sfirst, first);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int f = sfirst < kPoints ? sfirst : kPoints - 1;
+      slo = lo + w * f;
+      shi = lo + w * (f + 1);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const double theta = shi, beta = st[j].lz_beta;
+  const double top = st[j].lam_max + st[j].eps_eff;
+  const double prev = st[j].lz_theta;
+  st[j].lz_theta = theta;
+  if (theta > 0.0 && top > 0.0 && (p + 1.0) * theta / (2.0 * top) < mthr) {
+    st[j].sv_done = kLzShown;
+  } else if (!(theta > 0.0) || beta <= 1e-12 * top || m >= kLanczosMax || fabs(prev - theta) <= 1e-2 * theta) {
+    st[j].sv_done = kLzStop;
+  }
+}
+
+// Ends the iteration of a matrix with a verdict (one thread).
+__device__ __forceinline__ void lanczos_end(RootState* st) {
+  st->lz_done = 1;
+  if (st->sv_done == kLzShown) st->status = kMaxIter;  // certain to end unaccepted in fp32
+}
+
+// The test after the last step, which no tile pass follows.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void lanczos_test_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs,
+                                                               RootState* __restrict__ st, int p, double mthr) {
+  const int j = blockIdx.x;
+  if (j >= njobs) return;
+  lanczos_test(jobs, j, st, p, mthr);
+  if (threadIdx.x == 0 && st[j].status == kActive && st[j].sv_done != kLzOpen) lanczos_end(st + j);
+}
+
+// ---------------------------------------------------------------------------
 // Prologue.  MaxSV (Algorithm 1): power iteration on A_s = (A + A^T)/2 in
 // fp64 arithmetic, one workgroup per matrix, v0 = ones, Rayleigh quotient,
 // relative stop.
@@ -1248,12 +1366,17 @@ __global__ void root_warm_finish_kernel(const NewtonJob<T>* __restrict__ jobs, R
 // fence per workgroup would write back and invalidate the XCD L2s).
 // Vector layout per matrix (doubles): [0, n) vh, [n, n + T n) row partials
 // by tile column, [n + T n, n + 2 T n) column partials by tile row.
-// lanczos: the same pass for a Lanczos step (lanczos_reduce_kernel), gated
-// by that iteration's own stop flag.
-template <typename T>
+// LZ: the same pass for a Lanczos step (lanczos_reduce_kernel), gated by that
+// iteration's own stop flag.  Its first njobs workgroups run the witness test
+// of the step before (lanczos_test: chains of dependent fp64 divisions on one
+// workgroup per matrix) beside the tiles instead of between
+// two passes: a step of eight matrices of 2048^2 went from 83 to 55 us.  The
+// reduce launch after it takes up the verdict, so that no workgroup reads a
+// flag that its own launch writes; the tiles of that launch are not used.
+template <typename T, bool LZ>
 __global__ __launch_bounds__(kThreads) void maxsv_step_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs,
-                                                             const RootState* __restrict__ st, int total_full,
-                                                             int lanczos) {
+                                                             RootState* __restrict__ st, int total_full, int p,
+                                                             double mthr) {
   // the tile is staged in two halves of 64 rows (33 KB of LDS, so four
   // workgroups share a CU and hide each other's loads)
   constexpr int kHalf = kTile / 2;
@@ -1261,10 +1384,17 @@ __global__ __launch_bounds__(kThreads) void maxsv_step_kernel(const NewtonJob<T>
   __shared__ double vr[kTile], vc[kTile];       // v on the tile's rows and columns
   __shared__ double rsum[4][kHalf];             // row partials of a half, by column quarter
   __shared__ double csum[2][kTile];             // column partials, by row half of a half
-  const int t = blockIdx.x;
+  int t = blockIdx.x;
+  if constexpr (LZ) {
+    if (t < njobs) {
+      lanczos_test(jobs, t, st, p, mthr);
+      return;
+    }
+    t -= njobs;
+  }
   if (t >= total_full) return;
   const int j = find_job_full(jobs, njobs, t);
-  if (st[j].status != kActive || (lanczos ? st[j].lz_done : st[j].sv_done)) return;
+  if (st[j].status != kActive || (LZ ? st[j].lz_done : st[j].sv_done)) return;
   const NewtonJob<T>* J = jobs + j;
   const int n = J->n, TN = J->tiles_n;
   const int lt = t - J->full_begin;
@@ -1336,6 +1466,29 @@ __device__ __forceinline__ double sv_block_sum(double v, double* red) {
   return s;
 }
 
+// Row i of A v + A^T v: the two sums of the tile partials, each in order,
+// their loads eight at a time (eight matrices of 2048^2: 15.5 to 13.2 us a
+// reduction; one CU per matrix reading 524 KB of other XCDs' partials bounds it).
+__device__ __forceinline__ double sv_partials(const double* prow, const double* pcol, int n, int TN, int i) {
+  constexpr int kBatch = 8;
+  double a = 0.0, b = 0.0;
+  for (int c0 = 0; c0 < TN; c0 += kBatch) {
+    double pa[kBatch], pb[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int64_t at = (int64_t)(c0 + k < TN ? c0 + k : TN - 1) * n + i;
+      pa[k] = prow[at];
+      pb[k] = pcol[at];
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      a += c0 + k < TN ? pa[k] : 0.0;
+      b += c0 + k < TN ? pb[k] : 0.0;
+    }
+  }
+  return a + b;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kSvThreads) void maxsv_reduce_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs,
                                                                  RootState* __restrict__ st, double tol, double eps,
@@ -1350,12 +1503,7 @@ __global__ __launch_bounds__(kSvThreads) void maxsv_reduce_kernel(const NewtonJo
   double* pcol = J->vec + n + (int64_t)TN * n;
   double q = 0.0, s2 = 0.0;
   for (int i = threadIdx.x; i < n; i += kSvThreads) {
-    double a = 0.0, b = 0.0;
-    for (int k = 0; k < TN; ++k) {
-      a += prow[(int64_t)k * n + i];
-      b += pcol[(int64_t)k * n + i];
-    }
-    const double v = 0.5 * (a + b);
+    const double v = 0.5 * sv_partials(prow, pcol, n, TN, i);
     q += vh[i] * v;
     s2 += v * v;
     prow[i] = v;  // row partials of tile column 0 are consumed: reuse as v
@@ -1403,8 +1551,6 @@ __global__ void maxsv_init_kernel(const NewtonJob<T>* __restrict__ jobs, int njo
 // before.  Vector layout after MaxSV's: [n + 2 T n, 2 n + 2 T n) the previous
 // Lanczos vector, then alpha[kLanczosMax], beta[kLanczosMax].
 // ---------------------------------------------------------------------------
-constexpr int kLanczosMax = 96;
-
 template <typename T>
 __global__ void lanczos_init_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs, RootState* __restrict__ st) {
   const int j = blockIdx.x;
@@ -1418,36 +1564,26 @@ __global__ void lanczos_init_kernel(const NewtonJob<T>* __restrict__ jobs, int n
   }
   if (threadIdx.x == 0) {
     st[j].lz_done = st[j].status != kActive;
+    st[j].sv_done = kLzOpen;
     st[j].lz_steps = 0;
     st[j].lz_beta = 0.0;
     st[j].lz_theta = INFINITY;
   }
 }
 
-// Number of eigenvalues of the symmetric tridiagonal (a[0..m), b[0..m-1))
-// below x: negative pivots of the LDL^T factorisation of T - x I (Sturm).
-__device__ inline int sturm_below(const double* a, const double* b, int m, double x) {
-  int c = 0;
-  double d = 1.0;
-  for (int i = 0; i < m; ++i) {
-    d = a[i] - x - (i > 0 ? b[i - 1] * b[i - 1] / d : 0.0);
-    if (d == 0.0) d = -1e-300;  // an exact zero pivot counts as negative
-    c += d < 0.0;
-  }
-  return c;
-}
-
 // One Lanczos step per matrix from the tile pass's partials: w = A_d v -
 // beta_prev v_prev, alpha = w . v, w -= alpha v, beta = |w|, next v = w /
-// beta; then the witness test above.  mthr: m1 of the fp32 cap.
+// beta.
 template <typename T>
 __global__ __launch_bounds__(kSvThreads) void lanczos_reduce_kernel(const NewtonJob<T>* __restrict__ jobs, int njobs,
-                                                                   RootState* __restrict__ st, int p, double mthr,
-                                                                   int kmax) {
+                                                                   RootState* __restrict__ st) {
   __shared__ double red[kSvThreads / 64];
-  __shared__ double sa[kLanczosMax], sb[kLanczosMax];
   const int j = blockIdx.x;
   if (j >= njobs || st[j].status != kActive || st[j].lz_done) return;
+  if (st[j].sv_done != kLzOpen) {
+    if (threadIdx.x == 0) lanczos_end(st + j);
+    return;
+  }
   const NewtonJob<T>* J = jobs + j;
   const int n = J->n, TN = J->tiles_n;
   double* v = J->vec;
@@ -1460,12 +1596,7 @@ __global__ __launch_bounds__(kSvThreads) void lanczos_reduce_kernel(const Newton
   const int k = st[j].lz_steps;
   double q = 0.0;
   for (int i = threadIdx.x; i < n; i += kSvThreads) {
-    double a = 0.0, b = 0.0;
-    for (int c = 0; c < TN; ++c) {
-      a += prow[(int64_t)c * n + i];
-      b += pcol[(int64_t)c * n + i];
-    }
-    const double w = 0.5 * (a + b) + e * v[i] - bprev * vp[i];
+    const double w = 0.5 * sv_partials(prow, pcol, n, TN, i) + e * v[i] - bprev * vp[i];
     prow[i] = w;  // row partials of tile column 0 are consumed: reuse as w
     q += w * v[i];
   }
@@ -1481,57 +1612,11 @@ __global__ __launch_bounds__(kSvThreads) void lanczos_reduce_kernel(const Newton
     vp[i] = v[i];
     v[i] = beta > 0.0 ? prow[i] / beta : 0.0;
   }
-  for (int i = threadIdx.x; i < k; i += kSvThreads) {
-    sa[i] = al[i];
-    sb[i] = be[i];
-  }
-  __shared__ double slo, shi;
-  __shared__ int sfirst;
   if (threadIdx.x == 0) {
-    sa[k] = alpha;
     al[k] = alpha;
     be[k] = beta;
-  }
-  __syncthreads();
-  const int m = k + 1;
-  // smallest Ritz value: the Gershgorin interval, narrowed by three rounds of
-  // multisection (every thread counts the eigenvalues below its own point)
-  if (threadIdx.x == 0) {
-    double lo = INFINITY, hi = -INFINITY;
-    for (int i = 0; i < m; ++i) {
-      const double r = (i > 0 ? fabs(sb[i - 1]) : 0.0) + (i + 1 < m ? fabs(sb[i]) : 0.0);
-      lo = fmin(lo, sa[i] - r);
-      hi = fmax(hi, sa[i] + r);
-    }
-    slo = lo;
-    shi = hi;
-  }
-  for (int round = 0; round < 3; ++round) {
-    if (threadIdx.x == 0) sfirst = kSvThreads;
-    __syncthreads();
-    const double lo = slo, w = (shi - slo) / kSvThreads;
-    const double x = lo + w * (threadIdx.x + 1);
-    if (sturm_below(sa, sb, m, x) >= 1) atomicMin(&sfirst, (int)threadIdx.x);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const int f = sfirst < kSvThreads ? sfirst : kSvThreads - 1;
-      slo = lo + w * f;
-      shi = lo + w * (f + 1);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
-  const double theta = shi;
-  const double top = st[j].lam_max + e;
-  const double prev = st[j].lz_theta;
-  st[j].lz_steps = m;
-  st[j].lz_beta = beta;
-  st[j].lz_theta = theta;
-  if (theta > 0.0 && top > 0.0 && (p + 1.0) * theta / (2.0 * top) < mthr) {
-    st[j].status = kMaxIter;  // certain to end unaccepted in fp32: straight to fp64
-    st[j].lz_done = 1;
-  } else if (!(theta > 0.0) || beta <= 1e-12 * top || m >= kmax || fabs(prev - theta) <= 1e-2 * theta) {
-    st[j].lz_done = 1;
+    st[j].lz_steps = k + 1;
+    st[j].lz_beta = beta;
   }
 }
 

@@ -1543,13 +1543,13 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       const int last = k + 1 == prm->maxsv_steps;
       STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
         if (j32) {
-          hipLaunchKernelGGL(maxsv_step_kernel<float>, dim3(full), dim3(kThreads), 0, s, j32, njobs,
-                             (const RootState*)st, full, 0);
+          hipLaunchKernelGGL((maxsv_step_kernel<float, false>), dim3(full), dim3(kThreads), 0, s, j32, njobs, st, full,
+                             p, 0.0);
           hipLaunchKernelGGL(maxsv_reduce_kernel<float>, dim3(njobs), dim3(kSvThreads), 0, s, j32, njobs, st, mtol,
                              eps, last);
         } else {
-          hipLaunchKernelGGL(maxsv_step_kernel<double>, dim3(full), dim3(kThreads), 0, s, j64, njobs,
-                             (const RootState*)st, full, 0);
+          hipLaunchKernelGGL((maxsv_step_kernel<double, false>), dim3(full), dim3(kThreads), 0, s, j64, njobs, st, full,
+                             p, 0.0);
           hipLaunchKernelGGL(maxsv_reduce_kernel<double>, dim3(njobs), dim3(kSvThreads), 0, s, j64, njobs, st, mtol,
                              eps, last);
         }
@@ -1592,12 +1592,14 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
     }));
     for (int k = 0; k < kLanczosMax; ++k) {
       STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
-        hipLaunchKernelGGL(maxsv_step_kernel<float>, dim3(full), dim3(kThreads), 0, s, j32, njobs,
-                           (const RootState*)st, full, 1);
-        hipLaunchKernelGGL(lanczos_reduce_kernel<float>, dim3(njobs), dim3(kSvThreads), 0, s, j32, njobs, st, p, m1,
-                           kLanczosMax);
+        hipLaunchKernelGGL((maxsv_step_kernel<float, true>), dim3(njobs + full), dim3(kThreads), 0, s, j32, njobs, st,
+                           full, p, m1);
+        hipLaunchKernelGGL(lanczos_reduce_kernel<float>, dim3(njobs), dim3(kSvThreads), 0, s, j32, njobs, st);
       }));
     }
+    STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
+      hipLaunchKernelGGL(lanczos_test_kernel<float>, dim3(njobs), dim3(kThreads), 0, s, j32, njobs, st, p, m1);
+    }));
   }
   // warm phase; -1: unknown number of matrices handed to the cold start
   int warm_aborts = -1;
