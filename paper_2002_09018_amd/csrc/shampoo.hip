@@ -1678,7 +1678,9 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
         run64 = h->pinned[2 * kCountRing + 2] > 0;
       }
     }
-    if (!all_small) STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
+    // (newton_small_kernel leaves its results in place; a kept warm result may
+    // be in the workspace's X)
+    if (!all_small || warm) STATUS_TRY(launch(h, SHAMPOO_KCLASS_ROOT_AUX, s, [&] {
       hipLaunchKernelGGL(root_output_kernel<float>, dim3(flat), dim3(kThreads), 0, s, j32, njobs, st, flat, 0, p);
     }));
   }

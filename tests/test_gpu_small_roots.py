@@ -14,6 +14,7 @@ import pytest
 
 import oracle.shampoo_oracle as O
 from tests.gpu_util import gpu_env, host, rel, say, spd, to_dev
+from tests.test_gpu_warm import drift_case, warm_roots
 
 pytestmark = pytest.mark.gpu
 
@@ -103,3 +104,22 @@ def test_outcomes_and_mixed_call(env):
     # zero iterations: 1 x 1, p = 1, Frobenius scaling: z A = 1 exactly
     x, i = _roots(env, [np.array([[4.0]], np.float32)], p=1, eps=0.0, scaling=0, precision=B.PRECISION_FP32)
     assert i[0]["iters"] == 0 and float(x[0][0, 0]) == 0.25
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,p,tol,iters", [(96, 4, 1e-3, 1), (33, 2, 1e-3, 1), (128, 3, 1e-3, 1), (96, 4, 1e-6, 2)])
+def test_warm_call_of_small_matrices(env, prec, n, p, tol, iters):
+    """A warm call whose matrices are all small returns the kept warm result,
+    in whichever buffer its last iterate is.  The residuals (oracle: 3e-3 to
+    1.4e-2 before, at most 3.4e-4 after one iteration) are far from tol 1e-3.
+    Bounds as in the warm tests at larger sizes; the start X0 is 1.8e-3 or
+    more from the limit, so X0 itself would fail the second."""
+    say(f"small warm roots n={n} p={p} tol={tol} prec={prec}")
+    A, X0 = drift_case(n, 1e2, 3e-3, p, 7 * n + p)
+    (X,), (i,), (w,) = warm_roots(env, [A], [X0], p=p, eps=1e-6, tol=tol, precision=prec)
+    ref = O.coupled_newton_warm(A, p, X0, eps=1e-6, tol=tol)
+    assert not ref["warm_aborted"] and ref["warm_iters"] == iters
+    assert w[0] == 1 and i["status"] in (0, 1), (w, i)
+    assert w[1] == iters if iters == 1 else abs(int(w[1]) - iters) <= 1, w
+    e = rel(X, ref["X"])
+    assert e <= 1e-3 and e < 0.2 * rel(ref["X"], X0), (e, w)
