@@ -32,7 +32,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "1024² fp32 inverse-4th-roots/sec + stats+precondition step ms; fp32 MFMA util %"
-PEAK_F32_MFMA = 157.3   # TFLOP/s, MI355X dense fp32 matrix
+PEAK_F32_MFMA = 157.3   # TFLOP/s, MI355X dense fp32 matrix instructions
+PEAK_BF16 = 2500.0      # dense bf16
+# fp32 products run as six bf16 products of exact planes, bf16 x fp32 as three
+PEAK_F32 = PEAK_BF16 / 6
+PEAK_MIXED = PEAK_BF16 / 3
 PEAK_F64_MFMA = 78.6
 PEAK_HBM = 8000.0       # GB/s
 
@@ -324,7 +328,7 @@ def run_c4(args, torch, B):
     flops_stats = K * nb * 2 * d * d * (d + 1)
     flops_prec = K * nb * 4 * d ** 3
     bytes_graft = K * nb * d * d * 28
-    roof_ms = (flops_stats / PEAK_F32_MFMA + flops_prec / PEAK_F32_MFMA) / 1e9 / K + bytes_graft / PEAK_HBM / 1e6 / K
+    roof_ms = (flops_stats / PEAK_F32 + flops_prec / PEAK_F32) / 1e9 / K + bytes_graft / PEAK_HBM / 1e6 / K
     ms_step = elapsed * 1e3 / K
     prods = sum(newton_products(i, 4, True) for i in iters)
     out = {
@@ -346,11 +350,11 @@ def run_c4(args, torch, B):
     }
     kr = out["kernels"]
     out["roofline"] = {"kernel": "gemm_grouped_kernel (preconditioning, the step's largest phase)", "bound": "mfma",
-                       "achieved": kr["precond_tflops"], "peak": PEAK_F32_MFMA, "unit": "TFLOP/s",
-                       "frac": kr["precond_tflops"] / PEAK_F32_MFMA,
+                       "achieved": kr["precond_tflops"], "peak": PEAK_F32, "unit": "TFLOP/s",
+                       "frac": kr["precond_tflops"] / PEAK_F32,
                        "step_frac_of_phase_roofline": roof_ms / ms_step}
     rr = out["root_refresh"]
-    rr["newton_frac"] = rr["newton_tflops"] / PEAK_F32_MFMA
+    rr["newton_frac"] = rr["newton_tflops"] / PEAK_F32
     return out
 
 
@@ -705,7 +709,10 @@ def run_c5(args, torch, B):
     flops_stats = K * sum(m * (m + 1) * n + n * (n + 1) * m for m, n in shp)
     flops_prec = K * sum(2 * m * m * n + 2 * m * n * n for m, n in shp)
     bytes_graft = K * sum(m * n for m, n in shp) * 26     # bf16 G: 2 + 3 * 4 B pass 1, 3 * 4 B pass 2
-    roof_ms = ((flops_stats + flops_prec) / PEAK_F32_MFMA / 1e9 + bytes_graft / PEAK_HBM / 1e6) / K
+    # statistics bf16 x bf16, G Rr bf16 x fp32, Lr Z fp32 x fp32
+    flops_grr = K * sum(2 * m * n * n for m, n in shp)
+    ms_prec = (flops_grr / PEAK_MIXED + (flops_prec - flops_grr) / PEAK_F32) / 1e9
+    roof_ms = (flops_stats / PEAK_BF16 / 1e9 + ms_prec + bytes_graft / PEAK_HBM / 1e6) / K
     ms_step = elapsed * 1e3 / K
     ms_newton = rt["newton_f32"][0] + rt["newton_f64"][0]
     out = {
@@ -740,12 +747,13 @@ def run_c5(args, torch, B):
         },
     }
     kr = out["kernels"]
+    peak_prec = flops_prec / ms_prec / 1e9
     out["roofline"] = {"kernel": "gemm_grouped_kernel (preconditioning, the step's largest phase)", "bound": "mfma",
-                       "achieved": kr["precond_tflops"], "peak": PEAK_F32_MFMA, "unit": "TFLOP/s",
-                       "frac": kr["precond_tflops"] / PEAK_F32_MFMA,
+                       "achieved": kr["precond_tflops"], "peak": peak_prec, "unit": "TFLOP/s",
+                       "frac": kr["precond_tflops"] / peak_prec,
                        "step_frac_of_phase_roofline": roof_ms / ms_step}
     gr = out["grouped_roots"]
-    gr["newton_f32_frac"] = gr["newton_f32_tflops"] / PEAK_F32_MFMA if gr["newton_f32_tflops"] else None
+    gr["newton_f32_frac"] = gr["newton_f32_tflops"] / PEAK_F32 if gr["newton_f32_tflops"] else None
     gr["newton_f64_frac"] = gr["newton_f64_tflops"] / PEAK_F64_MFMA if gr["newton_f64_tflops"] else None
     return out
 
@@ -804,14 +812,14 @@ def run_c1(args, torch, B):
     }
     # useful flops of the ten steps: statistics (symmetric counting, both
     # sides), preconditioning (two products) and the roots' symmetric
-    # products; at the fp32-MFMA peak they take a microsecond or two, so the
+    # products; at the peak of fp32 products they take a microsecond or less, so the
     # step is bound by launch and synchronisation latency, not by a unit
     sym = n * n * (n + 1)
     flops = nsteps * (2 * sym + 4 * n ** 3) + sum(newton_products(i, 4, True) * sym for it in iters
                                           for i in it)
-    roof_us = flops / nsteps / (PEAK_F32_MFMA * 1e12) * 1e6
+    roof_us = flops / nsteps / (PEAK_F32 * 1e12) * 1e6
     out["roofline"] = {"kernel": "whole step (latency-bound)", "bound": "latency", "achieved": roof_us,
-                       "peak": us, "unit": "us at fp32-MFMA peak vs measured us", "frac": roof_us / us}
+                       "peak": us, "unit": "us at the fp32 product peak vs measured us", "frac": roof_us / us}
     return out
 
 
@@ -1057,19 +1065,20 @@ def run_c2(args, torch, B):
                    "blocks": nb, "n": n, "k": k, "p": p, "eps": eps, "root_scaling": args.scaling,
                    "graft": "separate calls" if args.split_graft else "fused into preconditioning"},
         "roofline": {
-            "kernel": "newton_stage_kernel<float> (grouped fp32-MFMA Newton products)",
-            "bound": "mfma", "achieved": achieved, "peak": PEAK_F32_MFMA, "unit": "TFLOP/s",
-            "frac": achieved / PEAK_F32_MFMA,
+            "kernel": "newton_stage_kernel<float> (grouped fp32 Newton products, six bf16 MFMA products each)",
+            "bound": "mfma", "achieved": achieved, "peak": PEAK_F32, "unit": "TFLOP/s",
+            "frac": achieved / PEAK_F32,
             "flops_per_launch": flops_newton32 / max(launches_newton, 1),
             "avg_launch_us": ms_newton * 1e3 / max(launches_newton, 1),
             "traffic": measured_traffic(),
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
         },
         "stats_precondition_ms_per_step": stats_prec_ms,
-        # both passes are fp32-MFMA bound: roofline time of their algorithmic
+        # both passes are MFMA bound (six bf16 products each): roofline time of their algorithmic
         # flops (symmetric counting for the statistics) over the measured time
-        "stats_precondition_roofline_frac": ((flops_stats + flops_prec) / args.steps / (PEAK_F32_MFMA * 1e12)
+        "stats_precondition_roofline_frac": ((flops_stats + flops_prec) / args.steps / (PEAK_F32 * 1e12)
                                              / (stats_prec_ms * 1e-3) if stats_prec_ms else None),
+        # against the fp32 matrix instructions, which the products no longer use
         "fp32_mfma_util": achieved / PEAK_F32_MFMA,
         "phases_ms_per_step": {c: v[0] / args.steps for c, v in times.items()},
         "launches_per_step": {c: v[1] / args.steps for c, v in times.items()},

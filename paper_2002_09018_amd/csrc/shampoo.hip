@@ -524,14 +524,12 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
       GemmProblem p{};  // Z = G Rr
       p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols;
       p.B = b.Rr; p.ldb = b.cols; p.b_rows = b.cols; p.b_cols = b.cols;
-     
       p.C = Z; p.ldc = b.cols; p.M = b.rows; p.N = b.cols; p.K = b.cols;
       p.alpha = 1.f; p.beta = 0.f;
       g_rr.push_back(p);
       g_rr_b.push_back(i);
       GemmProblem q{};  // P = Lr Z, Lr symmetric: read k-major
       q.A = b.Lr; q.lda = b.rows; q.a_rows = b.rows; q.a_cols = b.rows;
-     
       q.B = Z; q.ldb = b.cols; q.b_rows = b.rows; q.b_cols = b.cols;
       q.C = b.P; q.ldc = b.ld; q.M = b.rows; q.N = b.cols; q.K = b.rows;
       q.alpha = 1.f; q.beta = 0.f;
@@ -542,7 +540,6 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
       GemmProblem p{};  // P = G Rr
       p.A = b.G; p.lda = b.ld; p.a_rows = b.rows; p.a_cols = b.cols;
       p.B = b.Rr; p.ldb = b.cols; p.b_rows = b.cols; p.b_cols = b.cols;
-     
       p.C = b.P; p.ldc = b.ld; p.M = b.rows; p.N = b.cols; p.K = b.cols;
       p.alpha = 1.f; p.beta = 0.f;
       with_graft(p, b, i);
@@ -551,7 +548,6 @@ shampoo_status precond_impl(Handle* h, const shampoo_block* blocks, int nb, hipS
     } else if (b.Lr) {
       GemmProblem q{};  // P = Lr G
       q.A = b.Lr; q.lda = b.rows; q.a_rows = b.rows; q.a_cols = b.rows;
-     
       q.B = b.G; q.ldb = b.ld; q.b_rows = b.rows; q.b_cols = b.cols;
       q.C = b.P; q.ldc = b.ld; q.M = b.rows; q.N = b.cols; q.K = b.rows;
       q.alpha = 1.f; q.beta = 0.f;
