@@ -721,11 +721,11 @@ struct RootProduct<double, LA, LB> {
   typedef WaveAcc<double> Acc;
   static constexpr int bytes = 16;
   static __device__ __forceinline__ void run(Acc& acc, const Operand<double>& A, const Operand<double>& B, int m0,
-                                             int n0, int K, char*, bool) {
+                                             int n0, int K, char*, bool diag) {
     __shared__ __attribute__((aligned(16))) double a0[StageElems<double, LA>::value], a1[StageElems<double, LA>::value];
     __shared__ __attribute__((aligned(16))) double b0[StageElems<double, LB>::value], b1[StageElems<double, LB>::value];
     acc.zero();
-    tile_mma<double, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1);
+    tile_mma<double, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, diag);
   }
 };
 
@@ -800,7 +800,6 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
   const bool helper = diag && wave == 2;
   const int wm0 = m0 + (helper ? 0 : (wave >> 1) * kWaveTile), wn0 = n0 + (helper ? kWaveTile : (wave & 1) * kWaveTile);
   typedef Mfma<T> F;
-  constexpr int kNB = kWaveTile / F::kM;  // MFMA blocks of a wave, per side
   float rmax = 0.f;
   auto track = [&](T x, int r, int c) {
     if (resid) {
@@ -814,9 +813,9 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
   // written as one 16-byte store.
   if (sizeof(T) == 4 && !diag && m0 + kTile <= n && n0 + kTile <= n && (n & 3) == 0) {
 #pragma unroll
-    for (int i = 0; i < kNB; ++i)
+    for (int i = 0; i < WaveAcc<T>::NB; ++i)
 #pragma unroll
-      for (int jj = 0; jj < kNB; ++jj)
+      for (int jj = 0; jj < WaveAcc<T>::NB; ++jj)
 #pragma unroll
         for (int g = 0; g < F::kAcc / 4; ++g) {
           const int r = wm0 + i * F::kM + F::row(lane, 4 * g);
@@ -841,15 +840,15 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
   } else
   {
 #pragma unroll
-    for (int i = 0; i < kNB; ++i)
+    for (int i = 0; i < WaveAcc<T>::NB; ++i)
 #pragma unroll
-      for (int jj = 0; jj < kNB; ++jj)
+      for (int jj = 0; jj < WaveAcc<T>::NB; ++jj)
 #pragma unroll
         for (int v = 0; v < F::kAcc; ++v) {
           const int r = wm0 + i * F::kM + F::row(lane, v);
           const int c = wn0 + jj * F::kM + F::col(lane);
-          if (diag && wave == 1 && i >= kNB / 2) continue;
-          if (helper && i < kNB / 2) continue;
+          if (diag && wave == 1 && i >= WaveAcc<T>::NB / 2) continue;
+          if (helper && i < WaveAcc<T>::NB / 2) continue;
           if (r >= n || c >= n) continue;
           if (diag && r > c) continue;
           const T x = fin(acc.c[i][jj][v], r, c);
@@ -858,89 +857,6 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
           track(x, r, c);
         }
   }
-  if (resid) {
-    rmax = wave_max(rmax);
-    if (lane == 0 && rmax > 0.f) atomicMax(&st[j].resid_bits, __float_as_uint(rmax));
-  }
-}
-
-// The symmetric products in fp64 (same lists, maps and programs): workgroup
-// l takes half l & 1 (64 rows) of work item l >> 1, four waves of 32 x 64.
-// What bounds it: the fp64 matrix cores (77 TFLOP/s measured), and the end of
-// a launch: 8 matrices of 2048 are 1088 tiles, 4.25 for each compute unit, so
-// with whole tiles a launch lasted as long as 5 (and a compute unit left with
-// one workgroup has one wave per SIMD to hide everything behind).  Half tiles
-// round up to 4.5 and three workgroups share a compute unit instead of two.
-__global__ __launch_bounds__(kThreads, 3) void newton_half_kernel(const NewtonJob<double>* __restrict__ jobs,
-                                                                 const uint32_t* __restrict__ tlist,
-                                                                 const int* __restrict__ tcount,
-                                                                 RootState* __restrict__ st, NewtonStage S,
-                                                                 int mixed) {
-  typedef double T;
-  __shared__ __attribute__((aligned(16))) T a0[StageElems<T, kLayoutK, 64>::value], a1[StageElems<T, kLayoutK, 64>::value];
-  __shared__ __attribute__((aligned(16))) T b0[StageElems<T, kLayoutK>::value], b1[StageElems<T, kLayoutK>::value];
-  const int np = S.nprod;
-  const int nt = tcount[0], ne = tcount[1];
-  int l;
-  if (mixed) {
-    l = deal_chunks(blockIdx.x);
-    if (l >= 2 * np * nt) return;
-  } else {
-    l = xcd_split_remap(blockIdx.x, 2 * np * ne, 2 * np * (nt - ne));
-    if (l < 0) return;
-  }
-  const int half = l & 1;
-  l >>= 1;
-  const int t = l / np, prod = l - t * np;
-  const uint32_t code = tlist[t];
-  const int j = (int)(code >> 10), ti = (int)((code >> 5) & 31), tj = (int)(code & 31);
-  if (st[j].status != kActive) return;
-  const NewtonJob<T>* J = jobs + j;
-  const int n = J->n;
-  const int m0 = ti * kTile + 64 * half, n0 = tj * kTile;
-  if (m0 >= n) return;
-  const int par = st[j].parity;
-  const int ie = pick3(prod, S.q[0].e, S.q[1].e, S.q[2].e);
-  const bool resid = pick3(prod, S.q[0].resid, S.q[1].resid, S.q[2].resid) != 0;
-  const T ca = pick3(prod, S.q[0].ca, S.q[1].ca, S.q[2].ca);
-  const T cb = pick3(prod, S.q[0].cb, S.q[1].cb, S.q[2].cb);
-  const T cg = pick3(prod, S.q[0].cg, S.q[1].cg, S.q[2].cg);
-  const T* pa = newton_buf(J, par, pick3(prod, S.q[0].a, S.q[1].a, S.q[2].a));
-  const T* pb = newton_buf(J, par, pick3(prod, S.q[0].b, S.q[1].b, S.q[2].b));
-  T* pc = newton_buf(J, par, pick3(prod, S.q[0].dst, S.q[1].dst, S.q[2].dst));
-  const T* pe = ie >= 0 ? newton_buf(J, par, ie) : nullptr;
-  const bool al = (reinterpret_cast<uintptr_t>(pa) & 15) == 0 && (reinterpret_cast<uintptr_t>(pb) & 15) == 0 &&
-                  ((n * (int)sizeof(T)) & 15) == 0;
-  Operand<T> A{pa, n, n, n, al};
-  Operand<T> B{pb, n, n, n, al};
-  WaveAcc<T, 2, 4> acc;
-  acc.zero();
-  const bool diag = ti == tj;
-  half_mma<T, kLayoutK>(acc, A, B, m0, n0, n, a0, a1, b0, b1, diag, half);
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm0 = m0 + (wave >> 1) * 32, wn0 = n0 + (wave & 1) * kWaveTile;
-  typedef Mfma<T> F;
-  float rmax = 0.f;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int v = 0; v < F::kAcc; ++v) {
-        const int r = wm0 + i * F::kM + F::row(lane, v);
-        const int c = wn0 + jj * F::kM + F::col(lane);
-        if (r >= n || c >= n || r > c) continue;
-        T x = affine(ca, acc.c[i][jj][v], cb, pe ? gload<T>(pe + (int64_t)r * n + c) : (T)0);
-        if (r == c) x += cg;
-        gstore<T>(pc + (int64_t)r * n + c, x);
-        if (r != c) gstore<T>(pc + (int64_t)c * n + r, x);
-        if (resid) {
-          float d = (float)fabs((double)x - (r == c ? 1.0 : 0.0));
-          if (!(d <= 3.0e38f)) d = INFINITY;  // NaN or overflow
-          rmax = rmax > d ? rmax : d;
-        }
-      }
   if (resid) {
     rmax = wave_max(rmax);
     if (lane == 0 && rmax > 0.f) atomicMax(&st[j].resid_bits, __float_as_uint(rmax));
@@ -1065,12 +981,11 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_dense_kernel(const
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = m0 + (wave >> 1) * kWaveTile, wn0 = n0 + (wave & 1) * kWaveTile;
   typedef Mfma<T> F;
-  constexpr int kNB = kWaveTile / F::kM;  // MFMA blocks of a wave, per side
   float rmax = 0.f, cmax = 0.f;
 #pragma unroll
-  for (int i = 0; i < kNB; ++i)
+  for (int i = 0; i < WaveAcc<T>::NB; ++i)
 #pragma unroll
-    for (int jj = 0; jj < kNB; ++jj)
+    for (int jj = 0; jj < WaveAcc<T>::NB; ++jj)
 #pragma unroll
       for (int v = 0; v < F::kAcc; ++v) {
         const int r = wm0 + i * F::kM + F::row(lane, v);

@@ -855,17 +855,12 @@ shampoo_status newton_phase(Handle* h, const NewtonJob<T>* djobs, const TileList
                              tl.tcount, st, S);
         });
     }
-    // (padded for the chunked deal of matrices of different sizes; fp64: two
-    // workgroups per tile)
-    const int work = S.nprod * total_up * (sizeof(T) == 8 ? 2 : 1);
+    // (padded for the chunked deal of matrices of different sizes)
+    const int work = S.nprod * total_up;
     const int grid = tl.mixed ? cdiv(work, 8 * kDealChunk) * 8 * kDealChunk : 8 * (cdiv(work, 8) + 1);
     return launch(h, cls, s, [&] {
-      if constexpr (sizeof(T) == 8)
-        hipLaunchKernelGGL(newton_half_kernel, dim3(grid), dim3(kThreads), 0, s, djobs, tl.tlist, tl.tcount, st, S,
-                           tl.mixed);
-      else
-        hipLaunchKernelGGL(newton_stage_kernel<T>, dim3(grid), dim3(kThreads), 0, s, djobs, tl.tlist, tl.tcount,
-                           njobs, st, S, tl.mixed);
+      hipLaunchKernelGGL(newton_stage_kernel<T>, dim3(grid), dim3(kThreads), 0, s, djobs, tl.tlist, tl.tcount, njobs,
+                         st, S, tl.mixed);
     });
   };
   const bool power = scaling == SHAMPOO_SCALING_POWER4;

@@ -77,17 +77,16 @@ struct Mfma<double> {
 // contiguous runs (no pad needed: measured conflict-free).  kLayoutRow:
 // [128][kBK] rows padded by 16 bytes, so the 16-byte fragment reads of 8
 // consecutive rows fall in distinct banks and every row stays 16-byte aligned.
-template <typename T, int LAYOUT, int TW = kTile>
+template <typename T, int LAYOUT>
 struct Pitch {
   static constexpr int value =
-      LAYOUT == kLayoutK ? TW : Mfma<T>::kBK + 16 / (int)sizeof(T);
+      LAYOUT == kLayoutK ? kTile : Mfma<T>::kBK + 16 / (int)sizeof(T);
 };
 
-// Elements of one operand stage in LDS (TW: its width, 64 for the left
-// operand of a half tile).
-template <typename T, int LAYOUT, int TW = kTile>
+// Elements of one operand stage in LDS.
+template <typename T, int LAYOUT>
 struct StageElems {
-  static constexpr int value = (LAYOUT == kLayoutK ? Mfma<T>::kBK : TW) * Pitch<T, LAYOUT, TW>::value;
+  static constexpr int value = (LAYOUT == kLayoutK ? Mfma<T>::kBK : kTile) * Pitch<T, LAYOUT>::value;
   static_assert(value * (int)sizeof(T) % 16 == 0, "stages must stay 16-byte aligned");
 };
 
@@ -121,21 +120,21 @@ struct Operand {
 };
 
 // Per-thread staging registers for one operand stage (fp64).
-template <typename T, int LAYOUT, int TW = kTile>
+template <typename T, int LAYOUT>
 struct Loader {
   typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
   static constexpr int VE = 16 / (int)sizeof(T);
   static constexpr int BK = Mfma<T>::kBK;
-  static constexpr int NVEC = BK * TW / VE;
+  static constexpr int NVEC = BK * kTile / VE;
   static constexpr int PER = NVEC / kThreads;
-  static constexpr int LDP = Pitch<T, LAYOUT, TW>::value;
+  static constexpr int LDP = Pitch<T, LAYOUT>::value;
   static_assert(NVEC % kThreads == 0, "stage must split evenly over the workgroup");
   V buf[PER];
 
   // Storage coordinates (relative to the stage origin) of vector slot i.
   static __device__ __forceinline__ void slot(int tid, int i, int& sr, int& sc) {
     const int v = tid + i * kThreads;
-    constexpr int VPR = (LAYOUT == kLayoutK ? TW : BK) / VE;
+    constexpr int VPR = (LAYOUT == kLayoutK ? kTile : BK) / VE;
     sr = v / VPR;
     sc = (v % VPR) * VE;
   }
@@ -143,8 +142,8 @@ struct Loader {
   // Whether the stage with storage origin (r0, c0) lies inside the operand
   // and is 16-byte aligned (plain 16-byte loads, no bounds checks).
   static __device__ __forceinline__ bool full(const Operand<T>& op, int r0, int c0) {
-    constexpr int SR = LAYOUT == kLayoutK ? BK : TW;
-    constexpr int SC = LAYOUT == kLayoutK ? TW : BK;
+    constexpr int SR = LAYOUT == kLayoutK ? BK : kTile;
+    constexpr int SC = LAYOUT == kLayoutK ? kTile : BK;
     return op.aligned && (r0 + SR <= op.rows) && (c0 + SC <= op.cols);
   }
 
@@ -212,24 +211,25 @@ __device__ __forceinline__ WaveRole wave_role(int wave, bool diag) {
   return {0, kWaveTile, wave == 1 ? kBlocksTopHalf : kBlocksBottomHalf};
 }
 
-// Accumulators of one wave: an NBI x NBJ grid of MFMA blocks (64 x 64 in a
-// full tile, 32 x 64 in a half tile).
-template <typename T, int NBI = kWaveTile / Mfma<T>::kM, int NBJ = kWaveTile / Mfma<T>::kM>
+// Accumulators of one wave: an NB x NB grid of MFMA blocks covering 64 x 64.
+template <typename T>
 struct WaveAcc {
-  typename Mfma<T>::acc_t c[NBI][NBJ];
+  static constexpr int NB = kWaveTile / Mfma<T>::kM;
+  typename Mfma<T>::acc_t c[NB][NB];
 
   __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int i = 0; i < NBI; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < NBJ; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int v = 0; v < Mfma<T>::kAcc; ++v) c[i][j][v] = (T)0;
   }
 
   // The MFMA k-steps of one LDS stage (kBK / kK steps) over the wave's
-  // blocks.  D: blocks (i, j) with i + D <= j are computed (kAllBlocks: all).
-  template <int LA, int LB, int LDPA, int LDPB, int D>
+  // NB x NB blocks.  MODE (kBlocks*): the blocks of the wave's square that
+  // are computed.
+  template <int LA, int LB, int LDPA, int LDPB, int MODE>
   __device__ __forceinline__ void stage(const T* __restrict__ a, const T* __restrict__ b, int wm0,
                                         int wn0, int lane) {
     constexpr int KS = Mfma<T>::kBK / Mfma<T>::kK;  // k-steps per stage
@@ -241,30 +241,30 @@ struct WaveAcc {
     const int ml = lane % Mfma<T>::kM;
     // kLayoutK fragments: one element per k-step, double-buffered in
     // registers so the reads of step s+1 are issued before the MFMAs of s.
-    T fa[2][NBI], fb[2][NBJ];
+    T fa[2][NB], fb[2][NB];
     const T* pa = a + g * KS * LDPA + wm0 + ml;
     const T* pb = b + g * KS * LDPB + wn0 + ml;
     if (LA == kLayoutK) {
 #pragma unroll
-      for (int i = 0; i < NBI; ++i) fa[S0 & 1][i] = pa[S0 * LDPA + i * Mfma<T>::kM];
+      for (int i = 0; i < NB; ++i) fa[S0 & 1][i] = pa[S0 * LDPA + i * Mfma<T>::kM];
     }
     if (LB == kLayoutK) {
 #pragma unroll
-      for (int j = 0; j < NBJ; ++j) fb[S0 & 1][j] = pb[S0 * LDPB + j * Mfma<T>::kM];
+      for (int j = 0; j < NB; ++j) fb[S0 & 1][j] = pb[S0 * LDPB + j * Mfma<T>::kM];
     }
     // kLayoutRow fragments: VP k-steps per 16-byte read, read per chunk of
     // VP steps (the registers of one chunk only)
 #pragma unroll
     for (int cch = S0 / VP; cch < S1 / VP; ++cch) {
-      vec_t ra[LA == kLayoutRow ? NBI : 1], rb[LB == kLayoutRow ? NBJ : 1];
+      vec_t ra[LA == kLayoutRow ? NB : 1], rb[LB == kLayoutRow ? NB : 1];
       if (LA == kLayoutRow) {
 #pragma unroll
-        for (int i = 0; i < NBI; ++i)
+        for (int i = 0; i < NB; ++i)
           ra[i] = *reinterpret_cast<const vec_t*>(a + (wm0 + i * Mfma<T>::kM + ml) * LDPA + g * KS + cch * VP);
       }
       if (LB == kLayoutRow) {
 #pragma unroll
-        for (int j = 0; j < NBJ; ++j)
+        for (int j = 0; j < NB; ++j)
           rb[j] = *reinterpret_cast<const vec_t*>(b + (wn0 + j * Mfma<T>::kM + ml) * LDPB + g * KS + cch * VP);
       }
 #pragma unroll
@@ -274,19 +274,19 @@ struct WaveAcc {
         if (s + 1 < S1) {
           if (LA == kLayoutK) {
 #pragma unroll
-            for (int i = 0; i < NBI; ++i) fa[cur ^ 1][i] = pa[(s + 1) * LDPA + i * Mfma<T>::kM];
+            for (int i = 0; i < NB; ++i) fa[cur ^ 1][i] = pa[(s + 1) * LDPA + i * Mfma<T>::kM];
           }
           if (LB == kLayoutK) {
 #pragma unroll
-            for (int j = 0; j < NBJ; ++j) fb[cur ^ 1][j] = pb[(s + 1) * LDPB + j * Mfma<T>::kM];
+            for (int j = 0; j < NB; ++j) fb[cur ^ 1][j] = pb[(s + 1) * LDPB + j * Mfma<T>::kM];
           }
         }
         if (LA == kLayoutK || LB == kLayoutK) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < NBI; ++i)
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-          for (int j = 0; j < NBJ; ++j) {
-            if (i + D > j) continue;
+          for (int j = 0; j < NB; ++j) {
+            if (!block_used<MODE, NB>(i, j)) continue;
             c[i][j] = Mfma<T>::mma(LA == kLayoutRow ? ra[i][e] : fa[cur][i], LB == kLayoutRow ? rb[j][e] : fb[cur][j],
                                    c[i][j]);
           }
@@ -296,18 +296,17 @@ struct WaveAcc {
   }
 };
 
-constexpr int kAllBlocks = -64;
-
-// k-loop over LDS stages of one wave at (wm0, wn0) of a TA x 128 tile.  Stages
-// alternate between two buffer pairs; at the start of stage st the registers
-// loaded during stage st-1 are written as stage st+1, into the pair that stage
-// st-1 read (every wave left it at the barrier ending that stage), and the
-// loads of stage st+2 are issued.
-template <int D, int TA, typename T, int LA, int LB, int NBI, int NBJ>
-__device__ __forceinline__ void tile_loop(WaveAcc<T, NBI, NBJ>& acc, const Operand<T>& A, const Operand<T>& B, int m0,
-                                          int n0, int K, T* a0, T* a1, T* b0, T* b1, int wm0, int wn0) {
+// k-loop over LDS stages of one wave with square (wm0, wn0) and block set
+// MODE (each block set is a separate loop, so the wave-uniform choice costs
+// no registers inside the loop).  Stages alternate between two buffer pairs;
+// at the start of stage st the registers loaded during stage st-1 are written
+// as stage st+1, into the pair that stage st-1 read (every wave left it at
+// the barrier ending that stage), and the loads of stage st+2 are issued.
+template <int MODE, typename T, int LA, int LB>
+__device__ __forceinline__ void tile_loop(WaveAcc<T>& acc, const Operand<T>& A, const Operand<T>& B, int m0, int n0,
+                                          int K, T* a0, T* a1, T* b0, T* b1, int wm0, int wn0) {
   constexpr int BK = Mfma<T>::kBK;
-  typedef Loader<T, LA, TA> LdA;
+  typedef Loader<T, LA> LdA;
   typedef Loader<T, LB> LdB;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -330,34 +329,30 @@ __device__ __forceinline__ void tile_loop(WaveAcc<T, NBI, NBJ>& acc, const Opera
       lb.store(odd ? b0 : b1, tid);
     }
     if (st + 2 < nst) load((st + 2) * BK);
-    acc.template stage<LA, LB, LdA::LDP, LdB::LDP, D>(odd ? a1 : a0, odd ? b1 : b0, wm0, wn0, lane);
+    acc.template stage<LA, LB, LdA::LDP, LdB::LDP, MODE>(odd ? a1 : a0, odd ? b1 : b0, wm0, wn0, lane);
     __syncthreads();
   }
 }
 
-// Full k-loop of one 128 x 128 output tile of a general product (4 waves,
-// 64 x 64 each).
+// Full k-loop of one 128 x 128 output tile.
+//   A: layout LA; kLayoutK reads storage rows k (cols m0..), kLayoutRow
+//      reads storage rows m0.. (cols k).
+//   B: layout LB; kLayoutK reads storage rows k (cols n0..), kLayoutRow
+//      reads storage rows n0.. (cols k).
+// diag: diagonal tile of a symmetric output; the waves take the squares and
+// block sets of wave_role (the epilogue must use the same roles).
 template <typename T, int LA, int LB>
 __device__ __forceinline__ void tile_mma(WaveAcc<T>& acc, const Operand<T>& A, const Operand<T>& B, int m0, int n0,
-                                         int K, T* a0, T* a1, T* b0, T* b1) {
-  const int wave = threadIdx.x >> 6;
-  tile_loop<kAllBlocks, kTile, T, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, (wave >> 1) * kWaveTile,
-                                          (wave & 1) * kWaveTile);
-}
-
-// k-loop of half a 128 x 128 tile (64 rows; 4 waves, 32 x 64 each) of a
-// symmetric fp64 product.  diag: the tile is diagonal, and a wave computes the
-// 16 x 16 blocks on and above the diagonal: its 32 rows start `off` blocks
-// below its 64 columns (off >= 4: none of them).
-template <typename T, int L>
-__device__ __forceinline__ void half_mma(WaveAcc<T, 2, 4>& acc, const Operand<T>& A, const Operand<T>& B, int m0,
-                                         int n0, int K, T* a0, T* a1, T* b0, T* b1, bool diag, int half) {
-  const int wave = threadIdx.x >> 6, wm = (wave >> 1) * 32, wn = (wave & 1) * kWaveTile;
-  const int off = diag ? (half * 64 + wm - wn) / Mfma<T>::kM : kAllBlocks;
-  if (off >= 4) tile_loop<4, 64, T, L, L>(acc, A, B, m0, n0, K, a0, a1, b0, b1, wm, wn);
-  else if (off == 2) tile_loop<2, 64, T, L, L>(acc, A, B, m0, n0, K, a0, a1, b0, b1, wm, wn);
-  else if (off == 0) tile_loop<0, 64, T, L, L>(acc, A, B, m0, n0, K, a0, a1, b0, b1, wm, wn);
-  else tile_loop<kAllBlocks, 64, T, L, L>(acc, A, B, m0, n0, K, a0, a1, b0, b1, wm, wn);
+                                         int K, T* a0, T* a1, T* b0, T* b1, bool diag = false) {
+  const WaveRole ro = wave_role(threadIdx.x >> 6, diag);
+  if (ro.mode == kBlocksAll)
+    tile_loop<kBlocksAll, T, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, ro.wm, ro.wn);
+  else if (ro.mode == kBlocksUpper)
+    tile_loop<kBlocksUpper, T, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, ro.wm, ro.wn);
+  else if (ro.mode == kBlocksTopHalf)
+    tile_loop<kBlocksTopHalf, T, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, ro.wm, ro.wn);
+  else
+    tile_loop<kBlocksBottomHalf, T, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, ro.wm, ro.wn);
 }
 
 // Workgroup id -> logical tile index so that consecutive logical tiles land
