@@ -7,9 +7,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libshampoo.so")
 SOURCES = [os.path.join(HERE, "csrc", "shampoo.hip")]
-HEADERS = [os.path.join(HERE, "csrc", "kernels.hpp"), os.path.join(HERE, "csrc", "tile_mfma.hpp"), os.path.join(HERE, "csrc", "split_mfma.hpp"),
-           os.path.join(HERE, "csrc", "small_root.hpp"), os.path.join(HERE, "csrc", "direct_mma.hpp"), os.path.join(HERE, "csrc", "embedding.hpp"),
-           os.path.join(ROOT, "include", "shampoo.h")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("kernels.hpp", "tile_mfma.hpp", "fp32_block.hpp", "split_mfma.hpp",
+                                                   "direct_mma.hpp", "small_root.hpp", "embedding.hpp")]
+HEADERS.append(os.path.join(ROOT, "include", "shampoo.h"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 

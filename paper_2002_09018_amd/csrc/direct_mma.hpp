@@ -19,75 +19,28 @@
 
 namespace shp {
 
-// Fragment source of one wave: rows (kLayoutRow) or columns (kLayoutK) i0 +
-// (lane & 31) of an operand, the lane's 8 of 16 k; past the operand's end its
-// last row or column is read (those outputs are not stored), past K zeros.
+// The planes of a step's fragment.
 template <typename S, int LAYOUT>
-struct DirectFrag {
-  const S* p;
-  int64_t step;  // elements between consecutive k
-  int k;         // the lane's first k of the step
-  S v[8];
-  __device__ __forceinline__ void init(const Operand<S>& op, int i0, int lane) {
-    const int i = i0 + (lane & 31);
-    k = (lane >> 5) * 8;
-    if (LAYOUT == kLayoutRow) {
-      p = op.ptr + (int64_t)min(i, op.rows - 1) * op.ld;
-      step = 1;
-    } else {
-      p = op.ptr + min(i, op.cols - 1);
-      step = op.ld;
+__device__ __forceinline__ void frag_planes(const DirectFrag<S, LAYOUT>& x, bf16x8 (&f)[Planes<S>::n]) {
+  u32x4 a, b, c;
+  if constexpr (Planes<S>::n == 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = (uint32_t)x.v[2 * e] | ((uint32_t)x.v[2 * e + 1] << 16);
+    f[0] = __builtin_bit_cast(bf16x8, a);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint32_t t0, t1, t2;
+      split_pair(x.v[2 * e], x.v[2 * e + 1], t0, t1, t2);
+      a[e] = t0;
+      b[e] = t1;
+      c[e] = t2;
     }
+    f[0] = __builtin_bit_cast(bf16x8, a);
+    f[1] = __builtin_bit_cast(bf16x8, b);
+    f[2] = __builtin_bit_cast(bf16x8, c);
   }
-  __device__ __forceinline__ void load(int k0, int K) {
-    if (k0 + 16 <= K) {
-      const S* q = p + (k0 + k) * step;
-      if constexpr (LAYOUT == kLayoutRow && sizeof(S) == 4) {
-        const f32x4u a = gload_f4(q), b = gload_f4(q + 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = a[e];
-          v[4 + e] = b[e];
-        }
-      } else if constexpr (LAYOUT == kLayoutRow) {
-        const u32x4u a = gload_h8(q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[2 * e] = (S)(a[e] & 0xffffu);
-          v[2 * e + 1] = (S)(a[e] >> 16);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = gload<S>(q + e * step);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = k0 + k + e < K ? gload<S>(p + (k0 + k + e) * step) : (S)0;
-    }
-  }
-  __device__ __forceinline__ void planes(bf16x8 (&f)[Planes<S>::n]) const {
-    u32x4 a, b, c;
-    if constexpr (Planes<S>::n == 1) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = (uint32_t)v[2 * e] | ((uint32_t)v[2 * e + 1] << 16);
-      f[0] = __builtin_bit_cast(bf16x8, a);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        uint32_t t0, t1, t2;
-        split_pair(v[2 * e], v[2 * e + 1], t0, t1, t2);
-        a[e] = t0;
-        b[e] = t1;
-        c[e] = t2;
-      }
-      f[0] = __builtin_bit_cast(bf16x8, a);
-      f[1] = __builtin_bit_cast(bf16x8, b);
-      f[2] = __builtin_bit_cast(bf16x8, c);
-    }
-  }
-};
-
-typedef Mfma<float>::acc_t block_acc;
+}
 
 template <bool FIRST, int NPA, int NPB>
 __device__ __forceinline__ void direct_step(const bf16x8 (&fa)[NPA], const bf16x8 (&fb)[NPB], block_acc& c,
@@ -104,7 +57,7 @@ __device__ __forceinline__ void direct_step(const bf16x8 (&fa)[NPA], const bf16x
 }
 
 // The 32 x 32 block at (m0, n0), in the accumulator layout.  Non-finite
-// outputs are recomputed in fp32 (FIX, as fix_nonfinite).
+// outputs are recomputed in fp32 (FIX).
 template <bool FIX, typename SA, int LA, typename SB, int LB>
 __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Operand<SB>& B, int m0, int n0, int K) {
   constexpr int NPA = Planes<SA>::n, NPB = Planes<SB>::n;
@@ -130,16 +83,16 @@ __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Oper
 #pragma unroll 1
     for (int k = k0; k < k1; k += 32) {
       bf16x8 fa[NPA], fb[NPB];
-      a0.planes(fa);
-      b0.planes(fb);
+      frag_planes(a0, fa);
+      frag_planes(b0, fb);
       if (k + 32 < K) {
         a0.load(k + 32, K);
         b0.load(k + 32, K);
       }
       direct_step<decltype(first)::value, NPA, NPB>(fa, fb, c, t);
       if (k + 16 >= k1) break;
-      a1.planes(fa);
-      b1.planes(fb);
+      frag_planes(a1, fa);
+      frag_planes(b1, fb);
       if (k + 48 < K) {
         a1.load(k + 48, K);
         b1.load(k + 48, K);
@@ -162,22 +115,7 @@ __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Oper
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) c[v] += t[v];
-    if constexpr (FIX) {
-      bool bad = false;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) bad |= !(fabsf(c[v]) <= 3.402823466e38f);
-      if (__any(bad)) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (fabsf(c[v]) <= 3.402823466e38f) continue;
-          const int r = m0 + Mfma<float>::row(lane, v), col = n0 + Mfma<float>::col(lane);
-          float x = 0.f;
-#pragma unroll 1
-          for (int k = 0; k < K; ++k) x = fmaf(operand_at<SA, LA>(A, r, k), operand_at<SB, LB>(B, col, k), x);
-          c[v] = x;
-        }
-      }
-    }
+    if constexpr (FIX) fp32_repair<SA, LA, SB, LB>(c, A, B, m0, n0, K);
   }
   return c;
 }

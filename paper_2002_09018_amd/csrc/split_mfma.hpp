@@ -28,8 +28,8 @@
 // 2^-134).
 //
 // Infinities and values that round up to infinity in p0 turn into NaN in the
-// other planes; fix_nonfinite recomputes every non-finite output in plain
-// fp32, so such inputs give what an fp32 sum gives.
+// other planes; fp32_repair recomputes every non-finite output with the fp32
+// instruction (fp32_block.hpp), so such inputs give what an fp32 sum gives.
 //
 // Tile: 4 wave64s, 2 x 2, each 64 x 64 (2 x 2 blocks of 32 x 32, 64 + 64
 // accumulator registers; a bf16 x bf16 product, one per step, has no second
@@ -44,7 +44,7 @@
 
 #include <type_traits>
 
-#include "tile_mfma.hpp"
+#include "fp32_block.hpp"
 
 namespace shp {
 
@@ -52,11 +52,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// 16-byte and 4-byte vectors at element alignment (global loads only)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
-typedef uint32_t u32u __attribute__((aligned(2)));
 
 constexpr int kStepB = 4096;  // bytes of one plane of a 16-deep step: 128 rows x 16 k
 constexpr int kBlockB = 1024; // one 32-row block
@@ -83,18 +78,6 @@ struct SplitSteps {
   static constexpr int value = np == 6 ? 1 : 2;
   static constexpr int waves = np == 2 ? 4 : kMinWaves;
 };
-
-// Global loads at element alignment (the typedefs' alignment would be lost
-// on a template argument).
-__device__ __forceinline__ f32x4u gload_f4(const float* p) {
-  return *(const __attribute__((address_space(1))) f32x4u*)(p);
-}
-__device__ __forceinline__ u32x4u gload_h8(const uint16_t* p) {
-  return *(const __attribute__((address_space(1))) u32x4u*)(p);
-}
-__device__ __forceinline__ uint32_t gload_h2(const uint16_t* p) {
-  return *(const __attribute__((address_space(1))) u32u*)(p);
-}
 
 __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
   const f32x2 v = {x, y};
@@ -460,49 +443,35 @@ __device__ __forceinline__ void split_loop(SplitAcc<Planes<SA>::n, Planes<SB>::n
   }
 }
 
-// Element (tile row or column i, k) of an operand, in fp32.
-template <typename S, int LAYOUT>
-__device__ __forceinline__ float operand_at(const Operand<S>& op, int i, int k) {
-  const int64_t at = LAYOUT == kLayoutK ? (int64_t)k * op.ld + min(i, op.cols - 1)
-                                        : (int64_t)min(i, op.rows - 1) * op.ld + k;
-  return cvt<float, S>(gload<S>(op.ptr + at));
-}
-
-// Recomputes the non-finite outputs of a wave in fp32 (rare: an infinity, a
-// NaN or an overflow in the operands).  `epi`: the wave's own 32 x 64 floats
-// of LDS, so that the loop over the outputs can be rolled.
+// Recomputes the non-finite outputs of a wave (one copy of the code for its
+// four blocks: it is rarely taken and would quadruple the epilogue).
 template <int NPA, int NPB, typename SA, int LA, typename SB, int LB>
 __device__ __forceinline__ void fix_nonfinite(SplitAcc<NPA, NPB>& acc, const Operand<SA>& A, const Operand<SB>& B,
-                                              int wm0, int wn0, int K, float* epi, int lane) {
-  typedef Mfma<float> F;
+                                              int wm0, int wn0, int K) {
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) bad |= !(fabsf(acc.c[i][j][v]) <= 3.402823466e38f);
-  if (!__any(bad)) return;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) epi[(j * 16 + v) * 64 + lane] = acc.c[i][j][v];
+      for (int v = 0; v < 16; ++v) bad |= !finite_f32(acc.c[i][j][v]);
+  if (__builtin_expect(!__any(bad), 1)) return;
 #pragma unroll 1
-    for (int q = 0; q < 32; ++q) {
-      float x = epi[q * 64 + lane];
-      if (fabsf(x) <= 3.402823466e38f) continue;
-      const int r = wm0 + i * 32 + F::row(lane, q & 15), c = wn0 + (q >> 4) * 32 + F::col(lane);
-      x = 0.f;
-#pragma unroll 1
-      for (int k = 0; k < K; ++k) x = fmaf(operand_at<SA, LA>(A, r, k), operand_at<SB, LB>(B, c, k), x);
-      epi[q * 64 + lane] = x;
+  for (int q = 0; q < 4; ++q) {
+    block_acc x;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float lo = q & 1 ? acc.c[0][1][v] : acc.c[0][0][v], hi = q & 1 ? acc.c[1][1][v] : acc.c[1][0][v];
+      x[v] = q & 2 ? hi : lo;
     }
+    fp32_repair<SA, LA, SB, LB>(x, A, B, wm0 + (q >> 1) * 32, wn0 + (q & 1) * 32, K);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc.c[i][j][v] = epi[(j * 16 + v) * 64 + lane];
+    for (int v = 0; v < 16; ++v) {
+      acc.c[0][0][v] = q == 0 ? x[v] : acc.c[0][0][v];
+      acc.c[0][1][v] = q == 1 ? x[v] : acc.c[0][1][v];
+      acc.c[1][0][v] = q == 2 ? x[v] : acc.c[1][0][v];
+      acc.c[1][1][v] = q == 3 ? x[v] : acc.c[1][1][v];
+    }
   }
 }
 
@@ -524,9 +493,7 @@ __device__ __forceinline__ void split_mma(SplitAcc<Planes<SA>::n, Planes<SB>::n>
     split_loop<kBlocksBottomHalf, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   acc.fold();
   if constexpr (FIX && Planes<SA>::n + Planes<SB>::n > 2)
-    fix_nonfinite<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K,
-                                                                reinterpret_cast<float*>(smem + wave * 8192),
-                                                                threadIdx.x & 63);
+    fix_nonfinite<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K);
 }
 
 }  // namespace shp

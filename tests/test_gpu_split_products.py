@@ -172,5 +172,100 @@ def test_few_tiles_same_bits(env, m, n, pad, bf16):
             torch.cuda.synchronize()
             got.append([host(v.contiguous()) for v in (b.L, b.R, b.P, b.D, b.W, norms[:3])])
         for a, c, what in zip(*got, ("L", "R", "P", "D", "W", "norms")):
-            f = np.isfinite(a)
-            assert np.array_equal(f, np.isfinite(c)) and np.array_equal(a[f], c[f]), (what, left, right)
+            assert np.array_equal(a, c, equal_nan=True), (what, left, right)
+
+
+def _overflow(x):
+    """fp64 products as an fp32 result holds them (no sum here is near the limit)."""
+    return np.where(np.abs(x) > 3.5e38, np.sign(x) * np.inf, x)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("left,right", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("m,n", [(40, 70), (300, 520)])
+def test_non_finite_preconditioning(env, m, n, left, right, bf16):
+    """P of gradients with an infinity, a NaN and a value that rounds up to
+    infinity in bf16 (its bf16 form is the largest finite bf16): infinite or
+    NaN, with the infinity's sign, exactly where the fp32 sums are, and
+    accurate elsewhere; from the separate and the fused call, alone (few
+    tiles) and in a launch of many tiles, the same bits.  Roots of one sign
+    and 1e-3 in size keep the huge value's products finite."""
+    torch, B, dev, h = env
+    dt = torch.bfloat16 if bf16 else torch.float32
+    r = np.random.default_rng(m)
+    g = r.uniform(0.5, 1.0, (m, n)).astype(np.float32)
+    g[1, 2], g[m - 1, 5], g[m // 2, n - 1], g[2, n // 2] = np.inf, np.nan, 3.4e38, -np.inf
+    if bf16:
+        g[m // 2, n - 1] = 3.38e38
+    l, q = (1e-3 * a for a in (r.uniform(0.5, 1.0, (m, m)), r.uniform(0.5, 1.0, (n, n))))
+    l, q = (0.5 * (a + a.T).astype(np.float32) for a in (l, q))
+    G = to_dev(torch, g, dev).to(dt)
+    x = host(G.float()).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        if right:
+            x = _overflow(x @ q.astype(np.float64))
+        if left:
+            x = _overflow(l.astype(np.float64) @ x)
+
+    def block(G, l, q):
+        z = lambda: torch.zeros(G.shape[0], G.shape[1], device=dev)
+        return B.Block(G=G, W=z(), D=z(), P=z(), Lr=l if left else None, Rr=q if right else None)
+
+    ld, qd = to_dev(torch, l, dev), to_dev(torch, q, dev)
+    big = torch.zeros(1024, 1536, device=dev, dtype=dt)
+    fill = block(big, torch.eye(1024, device=dev), torch.eye(1536, device=dev))
+    say(f"non-finite P {m}x{n} bf16={bf16} left={left} right={right}")
+    got = []
+    for extra in ([], [fill]):
+        b = block(G, ld, qd)
+        B.shampoo_precondition(h, [b] + extra)
+        got.append(host(b.P))
+        B.shampoo_precondition_graft(h, [b] + extra, 0.0)
+        got.append(host(b.P))
+    f = np.isfinite(x)
+    assert f.any() or (left and right)
+    for y in got:
+        assert np.array_equal(y, got[0], equal_nan=True)
+    y = got[0].astype(np.float64)
+    assert np.array_equal(np.isnan(y), np.isnan(x)) and np.array_equal(y[np.isinf(x)], x[np.isinf(x)])
+    assert (np.abs(y[f] - x[f]) <= 1e-5 * np.abs(x[f])).all()
+
+
+@pytest.mark.parametrize("fill", ["one NaN", "one infinity", "all NaN", "all infinite"])
+def test_non_finite_gradients_cost(env, fill):
+    """A gradient that overflowed costs a small multiple of a finite one: the
+    repair is at most one more pass on the fp32 instruction, at 2/3 to 5/4 of
+    the rest (the limit leaves room for a busy machine; a loop in single lanes
+    took 10 to 100 times the finite call)."""
+    torch, B, dev, h = env
+
+    def timed(f):
+        best = float("inf")
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            f()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    n, count = 1024, 32
+    z = lambda: [torch.zeros(n, n, device=dev) for _ in range(count)]
+    G, W, D, P, L, R = ([torch.randn(n, n, device=dev) for _ in range(count)], *(z() for _ in range(5)))
+    root = torch.eye(n, device=dev) + 0.01
+    upd = B.PackedBlocks(h, [B.Block(G=G[i], W=W[i], D=D[i], P=P[i], Lr=root, Rr=root) for i in range(count)])
+    sts = B.PackedBlocks(h, [B.Block(G=G[i], L=L[i], R=R[i]) for i in range(count)])
+    run = lambda: (timed(lambda: B.shampoo_update_stats(h, sts)),
+                   timed(lambda: B.shampoo_precondition_graft(h, upd, 0.0)))
+    say(f"cost of non-finite gradients: {fill}")
+    fine = run()
+    for x in G:
+        v = float("nan") if "NaN" in fill else float("inf")
+        if "all" in fill:
+            x.fill_(v)
+        else:
+            x[n // 3, n // 2] = v
+    got = run()
+    say(f"finite {fine[0]:.3f} {fine[1]:.3f} ms, {fill} {got[0]:.3f} {got[1]:.3f} ms")
+    assert got[0] <= 4 * fine[0] and got[1] <= 4 * fine[1], (fine, got)
