@@ -56,8 +56,8 @@ __device__ __forceinline__ void direct_step(const bf16x8 (&fa)[NPA], const bf16x
     }
 }
 
-// The 32 x 32 block at (m0, n0), in the accumulator layout.  Non-finite
-// outputs are recomputed in fp32 (FIX).
+// The 32 x 32 block at (m0, n0), in the accumulator layout (FIX: non-finite
+// outputs are recomputed in fp32).
 template <bool FIX, typename SA, int LA, typename SB, int LB>
 __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Operand<SB>& B, int m0, int n0, int K) {
   constexpr int NPA = Planes<SA>::n, NPB = Planes<SB>::n;

@@ -1,11 +1,24 @@
-// 32 x 32 output blocks on the fp32 instruction, one wave each, operands read
-// from global memory straight into fragments: v_mfma_f32_32x32x2_f32 over
-// 16-deep steps.
+// 32 x 32 output blocks that the bf16 matrix cores should not form, one wave
+// each, operands read from global memory straight into fragments.
 //
-// The products of split_mfma.hpp are 2.7 times as fast.  This form takes what
-// they cannot: outputs they leave non-finite (an infinity or a NaN among the
-// operands, a value that rounds up to infinity in bf16, an overflow) are
-// recomputed here, so that they are what an fp32 sum gives.
+// The products of split_mfma.hpp are 2.7 times as fast as the fp32
+// instruction's.  What they cannot do as well:
+// - Contractions of at most kShortK (fp64_product).  The bf16 instruction cuts
+//   the products of a group of eight k at 2^-23 of the group's largest, and the
+//   split drops products of up to 2^-24; a long sum gains far more than that,
+//   a short one need not.  Root mean square error of a Gram matrix in units of
+//   2^-24, fp32 instruction against split: Gaussian rows 0.42 / 0.44 at K = 1;
+//   one column 30 times the others 0.42 / 0.57 at K = 2, 0.57 / 0.83 at 12, 1.5
+//   / 0.75 at 16; entries x exp(3 x), its diagonal 1.14 / 1.25 at 16, 1.30 /
+//   1.32 at 24, 1.53 / 1.33 at 32.  Such a product is bound by its output, so
+//   it is formed in fp64 (exact products, one rounding; 0.42 to 0.43
+//   everywhere) and costs no more (20 statistics of 1 x 4096 608 us, split 624,
+//   fp32 instruction 869; 40 of 16 x 4096 1287, 1209, 1477).  Up to K = 32 it
+//   would (60 of 32 x 2048 737, 506, 656).
+// - Outputs that the split leaves non-finite (an infinity or a NaN among the
+//   operands, a value that rounds up to infinity in bf16, an overflow): they
+//   are recomputed with v_mfma_f32_32x32x2_f32, so that they are what an fp32
+//   sum gives (fp32_repair).
 #pragma once
 
 #include "tile_mfma.hpp"
@@ -80,7 +93,16 @@ struct DirectFrag {
   }
 };
 
+// Element (tile row or column i, k) of an operand, in fp32.
+template <typename S, int LAYOUT>
+__device__ __forceinline__ float operand_at(const Operand<S>& op, int i, int k) {
+  const int64_t at = LAYOUT == kLayoutK ? (int64_t)k * op.ld + min(i, op.cols - 1)
+                                        : (int64_t)min(i, op.rows - 1) * op.ld + k;
+  return cvt<float, S>(gload<S>(op.ptr + at));
+}
+
 __device__ __forceinline__ bool finite_f32(float x) { return fabsf(x) <= 3.402823466e38f; }
+
 
 // The non-finite values of x, recomputed: block (m0, n0) of the product.  A
 // NaN stays one whatever follows, so the pass ends once every such value is
@@ -135,6 +157,61 @@ __device__ __forceinline__ void fp32_repair(block_acc& x, const Operand<SA>& A, 
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v) x[v] = finite_f32(x[v]) ? x[v] : c[v];
+}
+
+constexpr int kShortK = 16;
+
+// Block (m0, n0) of a product of 1 <= K <= kShortK.
+template <typename SA, int LA, typename SB, int LB>
+__device__ __forceinline__ block_acc fp64_product(const Operand<SA>& A, const Operand<SB>& B, int m0, int n0, int K) {
+  typedef Mfma<double> D;
+  const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
+  D::acc_t c[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) c[i][j][v] = 0.0;
+  // every operand first, then the products (a step at a time waited for its
+  // loads)
+  constexpr int kSteps = kShortK / D::kK;
+  float a[kSteps][2], b[kSteps][2];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int k = s * D::kK + g, at = min(k, K - 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a[s][i] = operand_at<SA, LA>(A, m0 + 16 * i + i16, at);
+      b[s][i] = operand_at<SB, LB>(B, n0 + 16 * i + i16, at);
+      if (k >= K) a[s][i] = b[s][i] = 0.f;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    if (s * D::kK >= K) break;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) c[i][j] = D::mma((double)a[s][i], (double)b[s][j], c[i][j]);
+  }
+  // to the layout of a 32 x 32 block: value v of a lane is row 8 (v / 4) + 4
+  // half + v % 4 of its column
+  block_acc x;
+  const int right = (lane >> 4) & 1, half = lane >> 5;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int src = ((v & 3) * 16 + i16) * 4, i = v >> 3, w = ((v >> 2) & 1) * 2;
+    float y[2][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        y[j][h] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int((float)c[i][j][w + h])));
+    const float lo = half ? y[0][1] : y[0][0], hi = half ? y[1][1] : y[1][0];
+    x[v] = right ? hi : lo;
+  }
+  return x;
 }
 
 }  // namespace shp

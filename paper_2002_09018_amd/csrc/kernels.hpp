@@ -184,8 +184,9 @@ __device__ __forceinline__ bool graft_vec(const GemmProblem& P, int m0, int n0) 
 // SGG (not void): element type of G for the fused graft pass 1 (problems
 // with gD set; a separate instantiation as well).
 // map: how workgroups find their tiles (kMapXcd, kMapDeal, kMapDiagLast).
-template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
-__global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_grouped_kernel(const GemmProblem* __restrict__ probs,
+// SHORT: the products of K <= kShortK, in fp64 (fp32_block.hpp).
+template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void, bool SHORT = false>
+__global__ __launch_bounds__(kThreads, (SHORT ? kMinWaves : SplitSteps<SA, SB>::waves)) void gemm_grouped_kernel(const GemmProblem* __restrict__ probs,
                                                                int nprob, int total_tiles, int map) {
   __shared__ __attribute__((aligned(16))) char smem[SplitShm<SA, SB>::bytes];
   // LIM: work depends on device-side counts and sits in the first logical
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
   constexpr int NB = 2;  // MFMA blocks of a wave, per side
   SplitAcc<Planes<SA>::n, Planes<SB>::n> acc;
   acc.zero();
-  split_mma<true, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, P.sym && ti == tj);
+  split_mma<SHORT ? kShort : (LIM ? kSplitRepairShort : kSplitRepair), SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, P.sym && ti == tj);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool diag = P.sym && ti == tj;
@@ -397,8 +398,8 @@ __global__ __launch_bounds__(kThreads, (SplitSteps<SA, SB>::waves)) void gemm_gr
 // The same products for launches of few tiles, one wave per 32 x 32 block
 // (direct_mma.hpp): workgroup b is block b & 15 of logical tile b >> 4.
 // Plain and symmetric outputs; a graft problem's P only (graft_tile_kernel
-// follows).
-template <typename SA, int LA, typename SB, int LB>
+// follows).  SHORT: the products of K <= kShortK, in fp64 (fp32_block.hpp).
+template <bool SHORT, typename SA, int LA, typename SB, int LB>
 __global__ __launch_bounds__(64) void gemm_direct_kernel(const GemmProblem* __restrict__ probs, int nprob) {
   const int t = blockIdx.x >> 4;
   const GemmProblem P = probs[find_problem_gemm(probs, nprob, t)];
@@ -415,7 +416,9 @@ __global__ __launch_bounds__(64) void gemm_direct_kernel(const GemmProblem* __re
   if (m0 >= P.M || n0 >= P.N || (P.sym && m0 > n0)) return;
   Operand<SA> A{reinterpret_cast<const SA*>(P.A), P.lda, P.a_rows, P.a_cols};
   Operand<SB> B{reinterpret_cast<const SB*>(P.B), P.ldb, P.b_rows, P.b_cols};
-  const block_acc acc = direct_mma<true, SA, LA, SB, LB>(A, B, m0, n0, P.K);
+  block_acc acc;
+  if constexpr (SHORT) acc = fp64_product<SA, LA, SB, LB>(A, B, m0, n0, P.K);
+  else acc = direct_mma<true, SA, LA, SB, LB>(A, B, m0, n0, P.K);
   typedef Mfma<float> F;
   const int lane = threadIdx.x, c = n0 + F::col(lane);
   if (c >= P.N) return;
@@ -713,7 +716,7 @@ struct RootProduct<float, LA, LB> {
                                              int n0, int K, char* smem, bool diag) {
     acc.zero();
     // a non-finite iterate stops its matrix (DIVERGED) whatever it holds
-    split_mma<false, float, LA, float, LB>(acc, A, B, m0, n0, K, smem, diag);
+    split_mma<kSplit, float, LA, float, LB>(acc, A, B, m0, n0, K, smem, diag);
   }
 };
 template <int LA, int LB>

@@ -295,8 +295,15 @@ constexpr int kDiagLastMinK = 2048;
 constexpr int kDirectTiles = 72;
 constexpr int kDirectRootTiles = 96;
 
-template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void>
+template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void, bool SHORT = false>
 shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t s, int cls) {
+  if constexpr (!LIM && !SHORT) {
+    // short contractions go to a launch of their own
+    const auto cut = std::stable_partition(probs.begin(), probs.end(), [](const GemmProblem& p) { return p.K > kShortK; });
+    std::vector<GemmProblem> rest(cut, probs.end());
+    probs.erase(cut, probs.end());
+    STATUS_TRY((run_gemm<SA, LA, SB, LB, false, SGG, true>(h, rest, s, cls)));
+  }
   if (probs.empty()) return SHAMPOO_OK;
   int total = 0, mixed = 0, sym = 1;
   for (const auto& p : probs) mixed |= p.M != probs[0].M || p.N != probs[0].N || p.K != probs[0].K;
@@ -327,7 +334,7 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
     if (total <= kDirectTiles) {
       const int np = (int)probs.size();
       return launch(h, cls, s, [&] {
-        hipLaunchKernelGGL((gemm_direct_kernel<SA, LA, SB, LB>), dim3(16 * total), dim3(64), 0, s,
+        hipLaunchKernelGGL((gemm_direct_kernel<SHORT, SA, LA, SB, LB>), dim3(16 * total), dim3(64), 0, s,
                            (const GemmProblem*)d, np);
         if constexpr (!std::is_same<SGG, void>::value) {
           for (const auto& p : probs)
@@ -339,7 +346,7 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
       });
     }
   }
-  auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG>;
+  auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG, SHORT>;
   const int lds = 0;  // static LDS
   const int np = (int)probs.size();
   STATUS_TRY(launch(h, cls, s, [&] {

@@ -28,7 +28,7 @@
 // 2^-134).
 //
 // Infinities and values that round up to infinity in p0 turn into NaN in the
-// other planes; fp32_repair recomputes every non-finite output with the fp32
+// other planes; fix_nonfinite recomputes every non-finite output with the fp32
 // instruction (fp32_block.hpp), so such inputs give what an fp32 sum gives.
 //
 // Tile: 4 wave64s, 2 x 2, each 64 x 64 (2 x 2 blocks of 32 x 32, 64 + 64
@@ -475,14 +475,38 @@ __device__ __forceinline__ void fix_nonfinite(SplitAcc<NPA, NPB>& acc, const Ope
   }
 }
 
+// How a product is formed: by the split alone, with its non-finite outputs
+// recomputed, that and short contractions in fp64 (where only the device knows
+// K), or in fp64 (launches of short contractions).
+enum { kSplit = 0, kSplitRepair = 1, kSplitRepairShort = 2, kShort = 3 };
+
+// The wave's blocks of a short contraction (those inside the output).
+template <int NPA, int NPB, typename SA, int LA, typename SB, int LB>
+__device__ __forceinline__ void short_blocks(SplitAcc<NPA, NPB>& acc, const Operand<SA>& A, const Operand<SB>& B,
+                                             int wm0, int wn0, int K) {
+  if (K <= 0) return;  // no active row: the sums are zero
+  const int rows = LA == kLayoutRow ? A.rows : A.cols, cols = LB == kLayoutRow ? B.rows : B.cols;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      __builtin_amdgcn_sched_barrier(0);  // one block's registers at a time
+      if (wm0 + 32 * i >= rows || wn0 + 32 * j >= cols) continue;
+      acc.c[i][j] = fp64_product<SA, LA, SB, LB>(A, B, wm0 + 32 * i, wn0 + 32 * j, K);
+    }
+}
+
 // Full k-loop of one 128 x 128 output tile; results in acc.c.  diag:
 // diagonal tile of a symmetric output (squares and block sets of wave_role).
-// FIX: recompute non-finite outputs in fp32.
-template <bool FIX, typename SA, int LA, typename SB, int LB>
+template <int MODE, typename SA, int LA, typename SB, int LB>
 __device__ __forceinline__ void split_mma(SplitAcc<Planes<SA>::n, Planes<SB>::n>& acc, const Operand<SA>& A,
                                           const Operand<SB>& B, int m0, int n0, int K, char* smem, bool diag) {
   const int wave = threadIdx.x >> 6;
   const WaveRole ro = wave_role(wave, diag);
+  if (MODE == kShort || (MODE == kSplitRepairShort && K <= kShortK)) {
+    short_blocks<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K);
+    return;
+  }
   if (ro.mode == kBlocksAll)
     split_loop<kBlocksAll, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   else if (ro.mode == kBlocksUpper)
@@ -492,7 +516,7 @@ __device__ __forceinline__ void split_mma(SplitAcc<Planes<SA>::n, Planes<SB>::n>
   else
     split_loop<kBlocksBottomHalf, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   acc.fold();
-  if constexpr (FIX && Planes<SA>::n + Planes<SB>::n > 2)
+  if constexpr (MODE != kSplit && Planes<SA>::n + Planes<SB>::n > 2)
     fix_nonfinite<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K);
 }
 

@@ -175,6 +175,38 @@ def test_few_tiles_same_bits(env, m, n, pad, bf16):
             assert np.array_equal(a, c, equal_nan=True), (what, left, right)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("m", [200, 1300])
+def test_short_contractions(env, m, bf16):
+    """Contractions of 1 to 33 with one column 30 times the others, alone
+    (few tiles; 1300 is many).  Up to 16 the sums are formed in fp64 and
+    rounded once (2^-24 of the result, and 2^-48 s for the sum itself); above,
+    they are within K 2^-24 s, one rounding per product."""
+    torch, B, dev, h = env
+    dt = torch.bfloat16 if bf16 else torch.float32
+    r = np.random.default_rng(m)
+    for K in (1, 2, 3, 4, 5, 12, 15, 16, 17, 33):
+        g = r.standard_normal((m, K))
+        g[:, K // 2] *= 30
+        G = to_dev(torch, g.astype(np.float32), dev).to(dt)
+        x = host(G.float()).astype(np.float64)
+        L, R = torch.zeros(m, m, device=dev), torch.zeros(K, K, device=dev)
+        q = r.standard_normal((K, K))
+        q = (0.5 * (q + q.T)).astype(np.float32)
+        P, Pt = torch.zeros(m, K, device=dev), torch.zeros(K, m, device=dev)
+        Q, Gt = to_dev(torch, q, dev), G.T.contiguous()
+        say(f"short contraction m={m} K={K} bf16={bf16}")
+        B.shampoo_update_stats(h, [B.Block(G=G, L=L, R=R)])
+        B.shampoo_precondition(h, [B.Block(G=G, P=P, Rr=Q)])
+        B.shampoo_precondition(h, [B.Block(G=Gt, P=Pt, Lr=Q)])
+        q = q.astype(np.float64)
+        for got, a, b in ((L, x, x.T), (P, x, q), (Pt, q, x.T)):
+            got, want = host(got).astype(np.float64), a @ b
+            s = np.abs(a) @ np.abs(b)
+            bound = 2.0 ** -24 * np.abs(want) + 2.0 ** -48 * s if a.shape[1] <= 16 else K * 2.0 ** -24 * s
+            assert (np.abs(got - want) <= bound).all(), (K, a.shape)
+
+
 def _overflow(x):
     """fp64 products as an fp32 result holds them (no sum here is near the limit)."""
     return np.where(np.abs(x) > 3.5e38, np.sign(x) * np.inf, x)
