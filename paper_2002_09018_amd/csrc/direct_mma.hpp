@@ -20,7 +20,7 @@
 namespace shp {
 
 // The planes of a step's fragment.
-template <typename S, int LAYOUT>
+template <bool SC, typename S, int LAYOUT>
 __device__ __forceinline__ void frag_planes(const DirectFrag<S, LAYOUT>& x, bf16x8 (&f)[Planes<S>::n]) {
   u32x4 a, b, c;
   if constexpr (Planes<S>::n == 1) {
@@ -31,7 +31,7 @@ __device__ __forceinline__ void frag_planes(const DirectFrag<S, LAYOUT>& x, bf16
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       uint32_t t0, t1, t2;
-      split_pair(x.v[2 * e], x.v[2 * e + 1], t0, t1, t2);
+      split_pair<SC>(x.v[2 * e], x.v[2 * e + 1], t0, t1, t2);
       a[e] = t0;
       b[e] = t1;
       c[e] = t2;
@@ -83,16 +83,16 @@ __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Oper
 #pragma unroll 1
     for (int k = k0; k < k1; k += 32) {
       bf16x8 fa[NPA], fb[NPB];
-      frag_planes(a0, fa);
-      frag_planes(b0, fb);
+      frag_planes<FIX>(a0, fa);
+      frag_planes<FIX>(b0, fb);
       if (k + 32 < K) {
         a0.load(k + 32, K);
         b0.load(k + 32, K);
       }
       direct_step<decltype(first)::value, NPA, NPB>(fa, fb, c, t);
       if (k + 16 >= k1) break;
-      frag_planes(a1, fa);
-      frag_planes(b1, fb);
+      frag_planes<FIX>(a1, fa);
+      frag_planes<FIX>(b1, fb);
       if (k + 48 < K) {
         a1.load(k + 48, K);
         b1.load(k + 48, K);
@@ -114,7 +114,7 @@ __device__ __forceinline__ block_acc direct_mma(const Operand<SA>& A, const Oper
       steps(k, min(K, k + kRun), std::false_type{});
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) c[v] += t[v];
+    for (int v = 0; v < 16; ++v) c[v] = (c[v] + t[v]) * (FIX ? split_down(NPA, NPB) : 1.f);
     if constexpr (FIX) fp32_repair<SA, LA, SB, LB>(c, A, B, m0, n0, K);
   }
   return c;

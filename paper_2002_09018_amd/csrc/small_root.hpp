@@ -100,7 +100,7 @@ struct SmallRoot {
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         uint32_t t0, t1, t2;
-        split_pair(x[4 * g + 2 * e], x[4 * g + 2 * e + 1], t0, t1, t2);
+        split_pair<false>(x[4 * g + 2 * e], x[4 * g + 2 * e + 1], t0, t1, t2);
         a[e] = t0;
         b[e] = t1;
         c[e] = t2;

@@ -4,13 +4,16 @@
 // An fp32 operand is split exactly into three bf16 planes while it is staged,
 //   x = p0 + p1 + p2,  p0 = bf16(x), p1 = bf16(x - p0), p2 = x - p0 - p1
 // (24 significant bits are three times 8; every difference is exact), and
-//   x y = p0 q0 + (p0 q1 + p1 q0) + (p1 q1 + p0 q2 + p2 q0) + O(2^-26 |x y|):
-// six v_mfma_f32_32x32x16_bf16, whose products are exact and whose sums are
-// rounded to nearest in fp32.  bf16 operands are one plane (one product for
-// bf16 x bf16, three for bf16 x fp32, both without any dropped term).
+//   x y = p0 q0 + (p0 q1 + p1 q0) + (p1 q1 + p0 q2 + p2 q0) + the rest,
+// at most 2^-24 |x y| (typically 2^-28): six v_mfma_f32_32x32x16_bf16.  Their
+// products are exact; the instruction adds k 0..7 and k 8..15 to the
+// accumulator one after the other, each sum rounded to nearest, but cuts the
+// products of such a group at 2^-23 of the largest.  bf16 operands are one
+// plane (one product for bf16 x bf16, three for bf16 x fp32, both without any
+// dropped term).
 //
-// Why: v_mfma_f32_32x32x2_f32 multiplies 256 flops per cycle and SIMD, the
-// bf16 instruction 1024 x 4 / 6 useful ones.  Two sets of accumulators keep
+// Why: v_mfma_f32_32x32x2_f32 gives 256 flops per cycle and compute unit, the
+// bf16 instruction 4096 / 6 useful ones.  Two sets of accumulators keep
 // the sums short: over the first kRun k-values the leading products go to one
 // and the five others to the other; then each further run of kRun k-values
 // collects its six products in the first, which is added to the second at the
@@ -23,9 +26,16 @@
 // products apart without runs lose more than fp32 on the diagonal of M M for
 // M = I + E with rows |E| = 1e-3 (6.1e-7 against 5.8e-7 at K = 2048; with
 // runs 1.3e-7), and so gave roots of 2048 x 2048 matrices 6.2e-7 from 64 bits
-// (fp32: 4.5e-7; with runs 1.6e-7).  Elements below about 2^-110 keep fewer
-// bits (their lower planes are bf16 subnormals, an absolute error of at most
-// 2^-134).
+// (fp32: 4.5e-7; with runs 1.6e-7).
+//
+// The planes of x below 2^-110 are bf16 subnormals and would lose bits (P of
+// gradients around 2^-115 was 1e-6 from 64 bits, around 2^-126 2e-3), so fp32
+// operands are split as 2^16 x, exact for every fp32 value, and the sums
+// multiplied by 2^-16 or 2^-32 at the end.  The multiplication costs 1 to 2.5%
+// of the call (two-sided updates of 1024 x 1024 9.1 -> 9.2 ms); it is left out
+// where every operand is near 1 (kSplit).  Sums at or above 2^96 (2^112 with
+// one fp32 operand) and elements at or above 2^112 overflow so and are
+// recomputed as the next paragraph tells.
 //
 // Infinities and values that round up to infinity in p0 turn into NaN in the
 // other planes; fix_nonfinite recomputes every non-finite output with the fp32
@@ -83,8 +93,16 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
   const f32x2 v = {x, y};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-// Two values into their three planes (pairs of bf16, x in the low half).
+// Two values into their three planes (pairs of bf16, x in the low half); SC:
+// of 2^16 times the values.
+constexpr float kSplitScale = 65536.f;
+
+template <bool SC>
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
+  if constexpr (SC) {
+    x *= kSplitScale;
+    y *= kSplitScale;
+  }
   p0 = pack_bf16(x, y);
   x -= __uint_as_float(p0 << 16);
   y -= __uint_as_float(p0 & 0xffff0000u);
@@ -98,14 +116,14 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& p0, uint3
 // kLayoutRow operand, the storage columns of a kLayoutK one).  Tile rows past
 // the operand's end are clamped to its last one (they only feed outputs that
 // are not stored); k-values at or past K are staged as zeros.
-template <typename S, int LAYOUT, int KS>
+template <typename S, int LAYOUT, int KS, bool SC>
 struct SplitLoader;
 
 // fp32, k contiguous: a thread takes 4 consecutive k of 2 KS rows.  Eight
 // consecutive lanes hold the two k quarters of a half for four rows, so the
 // 8-byte LDS writes of a wave are conflict-free.
-template <int KS>
-struct SplitLoader<float, kLayoutRow, KS> {
+template <int KS, bool SC>
+struct SplitLoader<float, kLayoutRow, KS, SC> {
   static constexpr int PER = 2 * KS;
   static constexpr int BK = 16 * KS;
   const float* p[PER];
@@ -153,7 +171,7 @@ struct SplitLoader<float, kLayoutRow, KS> {
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         uint32_t t0, t1, t2;
-        split_pair(v[i][2 * e], v[i][2 * e + 1], t0, t1, t2);
+        split_pair<SC>(v[i][2 * e], v[i][2 * e + 1], t0, t1, t2);
         a[e] = t0;
         b[e] = t1;
         c[e] = t2;
@@ -168,8 +186,8 @@ struct SplitLoader<float, kLayoutRow, KS> {
 // fp32, k the storage row: a thread takes one column and 8 consecutive k per
 // step, loaded as 8 row segments shared by the wave; the transposition is
 // the packing of its own registers.
-template <int KS>
-struct SplitLoader<float, kLayoutK, KS> {
+template <int KS, bool SC>
+struct SplitLoader<float, kLayoutK, KS, SC> {
   static constexpr int BK = 16 * KS;
   const float* p;
   float v[KS][8];
@@ -201,7 +219,7 @@ struct SplitLoader<float, kLayoutK, KS> {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         uint32_t t0, t1, t2;
-        split_pair(v[s][2 * e], v[s][2 * e + 1], t0, t1, t2);
+        split_pair<SC>(v[s][2 * e], v[s][2 * e + 1], t0, t1, t2);
         a[e] = t0;
         b[e] = t1;
         w[e] = t2;
@@ -214,8 +232,8 @@ struct SplitLoader<float, kLayoutK, KS> {
 };
 
 // bf16, k contiguous: a thread takes 8 consecutive k of KS rows.
-template <int KS>
-struct SplitLoader<uint16_t, kLayoutRow, KS> {
+template <int KS, bool SC>
+struct SplitLoader<uint16_t, kLayoutRow, KS, SC> {
   static constexpr int BK = 16 * KS;
   const uint16_t* p[KS];
   u32x4 v[KS];
@@ -266,8 +284,8 @@ struct SplitLoader<uint16_t, kLayoutRow, KS> {
 
 // bf16, k the storage row: a thread takes two neighbouring columns and 4
 // consecutive k per 16-deep step (4-byte loads of row segments).
-template <int KS>
-struct SplitLoader<uint16_t, kLayoutK, KS> {
+template <int KS, bool SC>
+struct SplitLoader<uint16_t, kLayoutK, KS, SC> {
   static constexpr int BK = 16 * KS;
   const uint16_t* p;
   bool pair, one;  // both columns inside the operand / at least the first
@@ -306,6 +324,11 @@ struct SplitLoader<uint16_t, kLayoutK, KS> {
   }
 };
 
+// What a product of scaled operands is multiplied by (bf16 ones are not scaled).
+constexpr float split_down(int npa, int npb) {
+  return (npa > 1 ? 1.f / kSplitScale : 1.f) * (npb > 1 ? 1.f / kSplitScale : 1.f);
+}
+
 constexpr int kRun = 256;  // k-values of one accumulation run
 
 // Accumulators of one wave (64 x 64): c the run in progress, t the first
@@ -336,14 +359,16 @@ struct SplitAcc {
           c[i][j][v] = 0.f;
         }
   }
+  template <bool SC>
   __device__ __forceinline__ void fold() {
     if (!kRuns) return;
+    constexpr float down = SC ? split_down(NPA, NPB) : 1.f;
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) c[i][j][v] += t[i][j][v];
+        for (int v = 0; v < 16; ++v) c[i][j][v] = (c[i][j][v] + t[i][j][v]) * down;
   }
   // One 16-deep step over the blocks of MODE; a, b: the step's planes at the
   // wave's first row block.  FIRST: a step of the first run.
@@ -389,7 +414,7 @@ struct SplitShm {
   static constexpr int bytes = 2 * stage < 32768 ? 32768 : 2 * stage;
 };
 
-template <int MODE, typename SA, int LA, typename SB, int LB>
+template <int MODE, bool SC, typename SA, int LA, typename SB, int LB>
 __device__ __forceinline__ void split_loop(SplitAcc<Planes<SA>::n, Planes<SB>::n>& acc, const Operand<SA>& A,
                                            const Operand<SB>& B, int m0, int n0, int K, char* smem, int wm0,
                                            int wn0) {
@@ -398,8 +423,8 @@ __device__ __forceinline__ void split_loop(SplitAcc<Planes<SA>::n, Planes<SB>::n
   const int tid = threadIdx.x, lane = tid & 63;
   const int nst = (K + BK - 1) / BK;
   if (nst <= 0) return;
-  SplitLoader<SA, LA, KS> la;
-  SplitLoader<SB, LB, KS> lb;
+  SplitLoader<SA, LA, KS, SC> la;
+  SplitLoader<SB, LB, KS, SC> lb;
   la.init(A, m0, tid);
   lb.init(B, n0, tid);
   la.load(A, 0, K, tid);
@@ -503,19 +528,20 @@ __device__ __forceinline__ void split_mma(SplitAcc<Planes<SA>::n, Planes<SB>::n>
                                           const Operand<SB>& B, int m0, int n0, int K, char* smem, bool diag) {
   const int wave = threadIdx.x >> 6;
   const WaveRole ro = wave_role(wave, diag);
+  constexpr bool SC = MODE != kSplit;
   if (MODE == kShort || (MODE == kSplitRepairShort && K <= kShortK)) {
     short_blocks<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K);
     return;
   }
   if (ro.mode == kBlocksAll)
-    split_loop<kBlocksAll, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
+    split_loop<kBlocksAll, SC, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   else if (ro.mode == kBlocksUpper)
-    split_loop<kBlocksUpper, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
+    split_loop<kBlocksUpper, SC, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   else if (ro.mode == kBlocksTopHalf)
-    split_loop<kBlocksTopHalf, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
+    split_loop<kBlocksTopHalf, SC, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
   else
-    split_loop<kBlocksBottomHalf, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
-  acc.fold();
+    split_loop<kBlocksBottomHalf, SC, SA, LA, SB, LB>(acc, A, B, m0, n0, K, smem, ro.wm, ro.wn);
+  acc.template fold<SC>();
   if constexpr (MODE != kSplit && Planes<SA>::n + Planes<SB>::n > 2)
     fix_nonfinite<Planes<SA>::n, Planes<SB>::n, SA, LA, SB, LB>(acc, A, B, m0 + ro.wm, n0 + ro.wn, K);
 }

@@ -207,6 +207,38 @@ def test_short_contractions(env, m, bf16):
             assert (np.abs(got - want) <= bound).all(), (K, a.shape)
 
 
+@pytest.mark.parametrize("exp", [-140, -126, -115, -108, 40, 55])
+@pytest.mark.parametrize("m,n", [(60, 100), (260, 700)])
+def test_tiny_and_huge_elements(env, m, n, exp):
+    """Gradients around 2^exp keep the accuracy of ordinary ones (the bound of
+    the edge tests; subnormal inputs are exact, so nothing is added for them):
+    P with roots around 2^60 (normal results) for the tiny ones and 1 for the
+    huge ones, whose statistics reach 2^120, and the statistics of tiny rows
+    beside rows around 1."""
+    torch, B, dev, h = env
+    r = np.random.default_rng(n)
+    g = r.standard_normal((m, n)) * 2.0 ** exp
+    if exp < 0:
+        g[::2] *= 2.0 ** -exp
+    g = g.astype(np.float32)
+    sc = 2.0 ** 60 if exp < 0 else 1.0
+    l, q = ((0.5 * (a + a.T) * sc).astype(np.float32) for a in (r.standard_normal((m, m)), r.standard_normal((n, n))))
+    tiny = g[1::2].copy()
+    x, t = g.astype(np.float64), tiny.astype(np.float64)
+    l = l[:len(t), :len(t)].copy()
+    Tt = to_dev(torch, tiny, dev)
+    L = torch.zeros(m, m, device=dev)
+    P, Q = (torch.zeros(*t.shape, device=dev) for _ in range(2))
+    say(f"elements around 2^{exp}, {m}x{n}")
+    B.shampoo_update_stats(h, [B.Block(G=to_dev(torch, g, dev), L=L)])
+    B.shampoo_precondition(h, [B.Block(G=Tt, P=P, Lr=to_dev(torch, l, dev)), B.Block(G=Tt, P=Q, Rr=to_dev(torch, q, dev))])
+    l, q = l.astype(np.float64), q.astype(np.float64)
+    for got, a, b in ((L, x, x.T), (P, l, t), (Q, t, q)):
+        got, want, s = host(got).astype(np.float64), a @ b, np.abs(a) @ np.abs(b)
+        ok = np.abs(got - want) <= _bound(a.shape[1], s) - 1e-37 + 2.0 ** -148
+        assert ok.all(), (a.shape, float((np.abs(got - want) / s).max()))
+
+
 def _overflow(x):
     """fp64 products as an fp32 result holds them (no sum here is near the limit)."""
     return np.where(np.abs(x) > 3.5e38, np.sign(x) * np.inf, x)
