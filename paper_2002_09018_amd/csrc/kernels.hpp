@@ -494,6 +494,7 @@ struct RootState {
   double lz_theta;   // its smallest Ritz value after the last step
   double z;          // scaling of M0 = z A_d: (1 + p) / (2 ||A_d||_F), times zc
   double zc;         // tightening factor of the power-bound scaling (1: Frobenius)
+  double lift;       // the cold fp32 iterates hold X times this (x_lift)
   double eps_eff;    // damping added
   double lam_max;    // MaxSV estimate (relative damping)
   double diag_min;   // smallest diagonal entry of A_d
@@ -705,22 +706,24 @@ __global__ __launch_bounds__(kThreads) void tile_list_kernel(const RootState* __
   build_tile_list(st, njobs, tmap, ubegin, diag_last, tlist, tcount);
 }
 
-// Tile product of the root kernels in either precision.
-template <typename T, int LA, int LB>
+// Tile product of the root kernels in either precision.  The cold iteration's
+// operands are near 1 (x_lift) and a non-finite iterate stops its matrix
+// (DIVERGED) whatever it holds: kSplit.  The warm start's hold the caller's X0
+// and A_d, of any size, and matrices of any n: kSplitRepairShort.
+template <typename T, int LA, int LB, int MODE>
 struct RootProduct;
-template <int LA, int LB>
-struct RootProduct<float, LA, LB> {
+template <int LA, int LB, int MODE>
+struct RootProduct<float, LA, LB, MODE> {
   typedef SplitAcc<3, 3> Acc;
   static constexpr int bytes = SplitShm<float, float>::bytes;
   static __device__ __forceinline__ void run(Acc& acc, const Operand<float>& A, const Operand<float>& B, int m0,
                                              int n0, int K, char* smem, bool diag) {
     acc.zero();
-    // a non-finite iterate stops its matrix (DIVERGED) whatever it holds
-    split_mma<kSplit, float, LA, float, LB>(acc, A, B, m0, n0, K, smem, diag);
+    split_mma<MODE, float, LA, float, LB>(acc, A, B, m0, n0, K, smem, diag);
   }
 };
-template <int LA, int LB>
-struct RootProduct<double, LA, LB> {
+template <int LA, int LB, int MODE>
+struct RootProduct<double, LA, LB, MODE> {
   typedef WaveAcc<double> Acc;
   static constexpr int bytes = 16;
   static __device__ __forceinline__ void run(Acc& acc, const Operand<double>& A, const Operand<double>& B, int m0,
@@ -746,7 +749,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
                                                                const int* __restrict__ tcount, int njobs,
                                                                RootState* __restrict__ st, NewtonStage S,
                                                                int mixed) {
-  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutK, kLayoutK>::bytes];
+  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutK, kLayoutK, kSplit>::bytes];
   const int np = S.nprod;
   const int nt = tcount[0], ne = tcount[1];
   int l;
@@ -787,8 +790,8 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_stage_kernel(const
   // All operands are symmetric, so both may be read in either layout: fp32
   // row-wise (k contiguous, as its LDS fragments are), fp64 k-major.
   constexpr int L = sizeof(T) == 4 ? kLayoutRow : kLayoutK;
-  typename RootProduct<T, L, L>::Acc acc;
-  RootProduct<T, L, L>::run(acc, A, B, m0, n0, n, smem, ti == tj);
+  typename RootProduct<T, L, L, kSplit>::Acc acc;
+  RootProduct<T, L, L, kSplit>::run(acc, A, B, m0, n0, n, smem, ti == tj);
   // value of output element (r, c) from its accumulator
   auto fin = [&](T v, int r, int c) -> T {
     T x = affine(ca, v, cb, pe ? gload<T>(pe + (int64_t)r * n + c) : (T)0);
@@ -940,7 +943,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_dense_kernel(const
                                                                           const int* __restrict__ tcount,
                                                                           int njobs, RootState* __restrict__ st,
                                                                           NewtonStage S, int mixed) {
-  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutRow, kLayoutK>::bytes];
+  __shared__ __attribute__((aligned(16))) char smem[RootProduct<T, kLayoutRow, kLayoutK, kSplitRepairShort>::bytes];
   const int np = S.nprod;
   const int nwork = np * *tcount;
   int l;
@@ -978,8 +981,8 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void newton_dense_kernel(const
   Operand<T> A{pa, n, n, n, al};
   Operand<T> B{pb, n, n, n, al};
 
-  typename RootProduct<T, kLayoutRow, kLayoutK>::Acc acc;
-  RootProduct<T, kLayoutRow, kLayoutK>::run(acc, A, B, m0, n0, n, smem, false);
+  typename RootProduct<T, kLayoutRow, kLayoutK, kSplitRepairShort>::Acc acc;
+  RootProduct<T, kLayoutRow, kLayoutK, kSplitRepairShort>::run(acc, A, B, m0, n0, n, smem, false);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = m0 + (wave >> 1) * kWaveTile, wn0 = n0 + (wave & 1) * kWaveTile;
@@ -1588,6 +1591,14 @@ __device__ __forceinline__ void sym_tile_pass(const float* __restrict__ A, int n
   }
 }
 
+// The X iterate is linear in its start X0 = z^(1/p) I and the split products
+// keep their accuracy only above 2^-110 (kSplit), so a root that small (p = 1,
+// statistics from 2^64 on) is iterated as 2^64 X and scaled by the output pass.
+template <typename T>
+__device__ __forceinline__ double x_lift(double z, int p) {
+  return sizeof(T) == 4 && pow(z, 1.0 / p) < 0x1p-64 ? 0x1p64 : 1.0;
+}
+
 // Per upper tile (ti <= tj): sum of s^2 over the tile, doubled off the
 // diagonal (the lower mirror has the same values), trace and minimum of the
 // diagonal.  Every element of A is read once from memory.
@@ -1653,8 +1664,10 @@ __global__ void root_prep_kernel(const NewtonJob<T>* __restrict__ jobs, int njob
     st[j].z = 0.0;
     return;
   }
-  st[j].z = (1.0 + p) / (2.0 * sqrt(fro2));
+  const double z = (1.0 + p) / (2.0 * sqrt(fro2));
+  st[j].z = z;
   st[j].zc = 1.0;
+  st[j].lift = x_lift<T>(z, p);
 }
 
 // M0 = z (A_s + eps I), X0 = z^(1/p) I (Algorithm 1 cold start); residual of
@@ -1674,7 +1687,7 @@ __global__ __launch_bounds__(kThreads) void root_init_kernel(const NewtonJob<T>*
   const int lt = t - J.full_begin;
   const int ti = lt / J.tiles_n, tj = lt % J.tiles_n;
   const double z = st[j].z, e = st[j].eps_eff;
-  const T x0 = (T)pow(z, 1.0 / p);
+  const T x0 = (T)(pow(z, 1.0 / p) * st[j].lift);
   const T a = (T)(p + 1) / (T)p, b = (T)-1 / (T)p;
   const int n = J.n;
   T* M = J.M[0];
@@ -1759,6 +1772,7 @@ __global__ void root_rescale_kernel(const NewtonJob<T>* __restrict__ jobs, int n
   c = c > 1.0 ? c : 1.0;  // never looser than the Frobenius bound
   st[j].zc = c;
   st[j].z *= c;
+  st[j].lift = x_lift<T>(st[j].z, p);
 }
 
 // M0 <- c M0 in place, X1 = z^(1/p) (a I + b M0), residual of M0.
@@ -1774,7 +1788,7 @@ __global__ __launch_bounds__(kThreads) void root_scale_kernel(const NewtonJob<T>
   const int ti = lt / J->tiles_n, tj = lt % J->tiles_n;
   const int n = J->n;
   const T c = (T)st[j].zc;
-  const T x0 = (T)pow(st[j].z, 1.0 / p);
+  const T x0 = (T)(pow(st[j].z, 1.0 / p) * st[j].lift);
   const T a = (T)(p + 1) / (T)p, b = (T)-1 / (T)p;
   T* M = J->M[0];
   T* X1 = J->X[1];
@@ -1874,7 +1888,7 @@ __global__ __launch_bounds__(kThreads) void newton_first4_kernel(const NewtonJob
   const double cd = st[j].zc;
   const T c = (T)cd, c2 = (T)(cd * cd), c4 = (T)(cd * cd * cd * cd);
   const T K1 = (T)k1, K2 = (T)k2, K3c = (T)(k3 * cd), K4 = (T)k4, K5c = (T)(k5 * cd);
-  const T x0 = (T)pow(st[j].z, 0.25);
+  const T x0 = (T)(pow(st[j].z, 0.25) * st[j].lift);
   const T a = (T)1.25, b = (T)-0.25;
   T* S0 = J->S[0];
   T* S1 = J->S[1];
@@ -1940,11 +1954,13 @@ __global__ void root_reset_kernel(RootState* __restrict__ st, int njobs, int pha
     s.diag_min = 0.0;
     s.z = 0.0;
     s.zc = 1.0;
+    s.lift = 1.0;
   } else if (!s.escalate) {
     return;
   } else {
     s.status = kActive;
     s.iters = 0;
+    s.lift = 1.0;
   }
   s.parity = 0;
   s.resid_bits = 0u;
@@ -2051,8 +2067,8 @@ __global__ __launch_bounds__(kThreads) void root_escalate_kernel(RootState* __re
 }
 
 // Writes the result into the caller's fp32 X: the final iterate when it sits
-// in a workspace buffer (fp32 parity 1, or any fp64 result, rounded), or
-// X0 = z^(1/p) I for a matrix that stopped before its first iteration.  Only
+// in a workspace buffer (fp32 parity 1, or any fp64 result, rounded) or is
+// lifted (x_lift), or X0 = z^(1/p) I for a matrix that stopped before its first iteration.  Only
 // matrices whose result came from this phase are touched (`phase_is_tail`
 // selects the fp64 tail of AUTO).
 template <typename T>
@@ -2069,7 +2085,8 @@ __global__ __launch_bounds__(kThreads) void root_output_kernel(const NewtonJob<T
   // a warm result at zero iterations is X0 itself, already the caller's X
   // (fp32) or in the current-X buffer (fp64)
   const bool ident = s.iters == 0 && s.warm != 1;
-  if (!ident && sizeof(T) == 4 && s.parity == 0) return;  // already in place
+  const float down = s.warm == 1 ? 1.f : (float)(1.0 / s.lift);
+  if (!ident && sizeof(T) == 4 && s.parity == 0 && down == 1.f) return;  // already in place
   const NewtonJob<T>* J = jobs + j;
   const T* src = J->X[s.parity];
   float* dst = J->Xout;
@@ -2078,12 +2095,12 @@ __global__ __launch_bounds__(kThreads) void root_output_kernel(const NewtonJob<T
   const int e0 = (t - J->flat_begin) * kFlatChunk, e1 = min(e0 + kFlatChunk, n * n);
   if (!ident && sizeof(T) == 4 && (n & 3) == 0) {
     for (int i = e0 + 4 * (int)threadIdx.x; i < e1; i += 4 * kThreads)
-      gstore<f4v>(dst + i, gload<f4v>(reinterpret_cast<const float*>(src) + i));
+      gstore<f4v>(dst + i, down * gload<f4v>(reinterpret_cast<const float*>(src) + i));
     return;
   }
   for (int i = e0 + (int)threadIdx.x; i < e1; i += kThreads) {
     const int r = i / n, c = i - r * n;
-    dst[i] = ident ? (r == c ? x0 : 0.f) : (float)src[i];
+    dst[i] = ident ? (r == c ? x0 : 0.f) : down * (float)src[i];
   }
 }
 

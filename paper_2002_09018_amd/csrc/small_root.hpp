@@ -207,7 +207,7 @@ struct SmallRoot {
     while ((p >> (top + 1)) != 0) ++top;
     const bool pow2 = (p & (p - 1)) == 0;
     int iters = 0, status = kActive, bit = 0;
-    float r = INFINITY, xs = 0.f;
+    float r = INFINITY, xs = 0.f, lift = 1.f;
     int op = q.power ? kOpSquare0 : -1;
     while (true) {
       if (op >= 0) {
@@ -316,7 +316,10 @@ struct SmallRoot {
         op = -1;
       }
       if (op == -1) {
-        xs = (float)(pow2 ? root2(z, top) : pow(z, 1.0 / p));
+        // as x_lift
+        const double x0 = pow2 ? root2(z, top) : pow(z, 1.0 / p);
+        lift = x0 < 0x1p-64 ? 0x1p64f : 1.f;
+        xs = (float)(x0 * lift);
         r = resid(M, (float)zc);
         if (!(r <= kDivergeAt)) status = kDiverged;
         else if (r <= q.tol) status = kConverged;
@@ -403,10 +406,11 @@ struct SmallRoot {
     // the last iterate, or X0 = z^(1/p) I
     {
       const int in = fresh(in_mask), dg = fresh(dg_mask);
+      const float down = 1.f / lift;
       float* out = J.Xout + (int64_t)(bi * 32 + F::row(lane, 0)) * n + bj * 32 + F::col(lane);
 #pragma unroll
       for (int v = 0; v < 16; ++v)
-        if ((in >> v) & 1) gstore<float>(out + F::row(0, v) * n, iters > 0 ? X[v] : (((dg >> v) & 1) ? xs : 0.f));
+        if ((in >> v) & 1) gstore<float>(out + F::row(0, v) * n, down * (iters > 0 ? X[v] : (((dg >> v) & 1) ? xs : 0.f)));
     }
     if (lead) {
       st.eps_eff = e;
@@ -417,6 +421,7 @@ struct SmallRoot {
       st.iters = iters;
       st.resid = r;
       st.parity = 0;  // the result is in the caller's X
+      st.lift = 1.0;
     }
   }
 };

@@ -123,3 +123,25 @@ def test_warm_call_of_small_matrices(env, prec, n, p, tol, iters):
     assert w[1] == iters if iters == 1 else abs(int(w[1]) - iters) <= 1, w
     e = rel(X, ref["X"])
     assert e <= 1e-3 and e < 0.2 * rel(ref["X"], X0), (e, w)
+
+
+@pytest.mark.parametrize("count", [1, 40])
+@pytest.mark.parametrize("n", [33, 128, 200])
+@pytest.mark.parametrize("scaling", [0, 1])
+def test_inverses_of_huge_statistics(env, n, count, scaling):
+    """p = 1 and eigenvalues of 2^118 to 2^121: X is around 2^-120 and its
+    iterate must not lose bits for that.  Same accuracy as for eigenvalues of 1
+    to 8 (within a half and 2^-21 for the other rounding of the scaled input);
+    one matrix and 40 (every launch form), and a warm call that keeps X0."""
+    torch, B, dev, h = env
+    say(f"inverses of huge statistics n={n} count={count} scaling={scaling}")
+    errs = []
+    for sc in (1.0, 2.0 ** 118):
+        A = (spd(n, 8.0, n).astype(np.float64) * sc).astype(np.float32)
+        xs, info = _roots(env, [A] * count, p=1, scaling=scaling, eps=0.0, precision=B.PRECISION_FP32)
+        assert all(i["status"] in (B.ROOT_CONVERGED, B.ROOT_STAGNATED) for i in info)
+        want = np.linalg.inv(A.astype(np.float64))
+        errs.append(max(rel(x, want) for x in (xs[0], xs[-1])))
+    assert errs[1] <= 1.5 * errs[0] + 2.0 ** -21, errs
+    (X,), (i,), (w,) = warm_roots(env, [A], [want.astype(np.float32)], p=1, eps=0.0, tol=1e-6, precision=1)
+    assert w[0] == 1 and rel(X, want) <= 1.5 * errs[0] + 2.0 ** -21, (w, i, rel(X, want))
