@@ -14,6 +14,17 @@
 // whole.  Waves of blocks on and above the diagonal multiply (10 of 16 at
 // NB = 4, at most three to a SIMD); the others take the mirrored values
 // through LDS, so iterates stay exactly symmetric.
+//
+// Once the residual is below 1/2 (where the subtraction is exact), M is held as
+// E = M - I and the powers of M1 as Q = M1^(2^s) - I: products of matrices near
+// I lose the small terms that the bf16 instruction sums together with a
+// diagonal product (split_mfma.hpp); those of E and Q are small themselves.
+// (Far from I the matrices themselves keep small eigenvalues to more bits: with
+// E from the start and the Frobenius scaling p = 1 roots lost 40%, and with Q a
+// 1 x 1 root of order 16 lost 4e-5.)  Roots of 24
+// Wishart matrices of 32 x 32, error in 2^-24, before / now / fp32 instruction
+// in the grouped path: p = 1 9.6 / 5.3 / 6.7, p = 2 3.7 / 1.4 / 2.9, p = 8 5.2 /
+// 1.4 / 2.6; the number of products is the same.
 #pragma once
 
 #include "kernels.hpp"
@@ -21,6 +32,9 @@
 namespace shp {
 
 constexpr int kSmallMax = 128;       // largest n
+// E shrinks below anything an M in 32 bits could show: a residual of at most
+// this that was still above tol ends the iteration as the rounding floor.
+constexpr float kSmallFloor = 0x1p-20f;
 constexpr int kSmallThreads = 1024;  // 16 waves; a matrix of NB^2 < 16 blocks uses the first NB^2
 // planes of a 128-wide operand pair, ten 32 x 33 exchange blocks, reductions
 constexpr int kSmallExchange = 32 * 33;  // floats of one exchanged block (padded rows)
@@ -38,10 +52,10 @@ enum : int {
   kOpSquare0,  // power bound: P = M0 M0
   kOpSquare1,  //              X = P P
   kOpFirst4,   // first M update at p = 4 under the power bound, one product
-  kOpX,        // X = X M1 = b X M + a X
-  kOpMM,       // P = M M, then P = M1 M1 and, for odd p, M = M1 M
-  kOpY,        // M = P M (bit s of p)
-  kOpP         // P = P P
+  kOpX,        // X = X M1 = b X M + a X, or b X E + X
+  kOpMM,       // P = M M, then P = M1 M1 and, for odd p, M = M1 M (or E E, Q and E)
+  kOpY,        // M = P M, or E = (I + Q)(I + E) - I (bit s of p)
+  kOpP         // P = P P, or Q = (I + Q)(I + Q) - I
 };
 
 // A small matrix's root is a chain of products with little work in each, run
@@ -131,13 +145,13 @@ struct SmallRoot {
     for (int w = 1; w < waves; ++w) s = s > red[w] ? s : red[w];
     return s;
   }
-  // max |scale x - I| over the matrix (infinity for a non-finite entry)
-  __device__ __forceinline__ float resid(const blk& x, float scale) {
+  // max |scale x - eye I| over the matrix (infinity for a non-finite entry)
+  __device__ __forceinline__ float resid(const blk& x, float scale, float eye) {
     float m = 0.f;
     const int dg = fresh(dg_mask), in = fresh(in_mask);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      float d = fabsf(scale * x[v] - (float)((dg >> v) & 1));
+      float d = fabsf(scale * x[v] - ((dg >> v) & 1 ? eye : 0.f));
       d = d <= 3.0e38f ? d : INFINITY;
       m = fmaxf(m, (in >> v) & 1 ? d : 0.f);
     }
@@ -208,6 +222,7 @@ struct SmallRoot {
     const bool pow2 = (p & (p - 1)) == 0;
     int iters = 0, status = kActive, bit = 0;
     float r = INFINITY, xs = 0.f, lift = 1.f;
+    bool near = false;  // M holds E
     int op = q.power ? kOpSquare0 : -1;
     while (true) {
       if (op >= 0) {
@@ -256,7 +271,7 @@ struct SmallRoot {
           }
         }
         // the affine term in X of op X and of the first update
-        const float ca = op == kOpX ? (float)b : 1.f, cb = op == kOpX ? (float)a : 1.f;
+        const float ca = op == kOpX ? (float)b : 1.f, cb = op == kOpX && !near ? (float)a : 1.f;
         const bool affine = op == kOpX || op == kOpFirst4;
         float* mine = ex + (wave < upper ? wave : 0) * kSmallExchange;
         if (wave < upper) {
@@ -284,7 +299,10 @@ struct SmallRoot {
           for (int v = 0; v < 16; ++v) X[v] = c[v];
         } else if (op == kOpY) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) M[v] = c[v];
+          for (int v = 0; v < 16; ++v) M[v] = (near ? P[v] + M[v] : 0.f) + c[v];
+        } else if (op == kOpP) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) P[v] = (near ? 2.f * P[v] : 0.f) + c[v];
         } else if (op == kOpFirst4) {
           const float c1 = (float)zc;
           const int dg = fresh(dg_mask);
@@ -320,7 +338,7 @@ struct SmallRoot {
         const double x0 = pow2 ? root2(z, top) : pow(z, 1.0 / p);
         lift = x0 < 0x1p-64 ? 0x1p64f : 1.f;
         xs = (float)(x0 * lift);
-        r = resid(M, (float)zc);
+        r = resid(M, (float)zc, 1.f);
         if (!(r <= kDivergeAt)) status = kDiverged;
         else if (r <= q.tol) status = kConverged;
         if (status != kActive) break;
@@ -363,10 +381,11 @@ struct SmallRoot {
         updated = true;
       } else {
         if (op == kOpMM) {
-          // M^2 -> M1^2 = b^2 M^2 + 2ab M + a^2 I, M1 M = b M^2 + a M
+          // M^2 -> M1^2 = b^2 M^2 + 2ab M + a^2 I, M1 M = b M^2 + a M;
+          // E^2 -> M1^2 - I = b^2 E^2 + 2b E, M1 M - I = b E^2 + (1 + b) E
           bit = 0;
-          const float b2 = (float)(b * b), ab2 = (float)(2.0 * a * b), a2 = (float)(a * a), b1 = (float)b,
-                      a1 = (float)a;
+          const float b2 = (float)(b * b), ab2 = (float)(near ? 2.0 * b : 2.0 * a * b),
+                      a2 = near ? 0.f : (float)(a * a), b1 = (float)b, a1 = (float)(near ? 1.0 + b : a);
           const int dg = fresh(dg_mask);
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
@@ -393,14 +412,20 @@ struct SmallRoot {
         }
       }
       const float prev = r;
-      r = resid(M, 1.f);
+      r = resid(M, 1.f, near ? 0.f : 1.f);
       ++iters;
       if (!(r <= kDivergeAt)) status = kDiverged;
       else if (r <= q.tol) status = kConverged;
-      else if (prev < kStagGate && r >= prev) status = kStagnated;
+      else if (prev < kStagGate && (r >= prev || prev <= kSmallFloor)) status = kStagnated;
       else if (iters >= q.max_iters) status = kMaxIter;
       else if (q.esc_thr && iters <= q.esc_n && r > q.esc_thr[iters - 1]) status = kMaxIter;
       if (status != kActive) break;
+      if (!near && r < 0.5f) {
+        near = true;
+        const int dg = fresh(dg_mask);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) M[v] -= (dg >> v) & 1 ? 1.f : 0.f;
+      }
       op = kOpX;
     }
     // the last iterate, or X0 = z^(1/p) I

@@ -5,9 +5,15 @@ of damping, against the oracle; a zero-iteration start, a NOT_PD matrix and an
 escalated one; and a mixed call, whose small matrices must come out bit for
 bit as in a call of their own.
 
-Tolerance: each iteration's fp32 rounding (sqrt(n) 2^-24 of the iterate)
-amplified by the condition number and the order, iters p kappa sqrt(n) 2^-24
-relative (Frobenius).
+Tolerance (relative, Frobenius), u = 2^-24: M0 = z (A + eps I) rounded to fp32 is
+a perturbation of u that the root amplifies by kappa / p (or by that of the first
+update, if larger: 66000 at p = 16, where it takes eigenvalues of 8.5 to 3e-4); X
+is rounded at each of the iters products; and the last residual r (per element, so at most n r in norm)
+is not followed by another update of X, which leaves n r / p:
+  err <= 2 (kappa / p + iters) u + n r / p,
+the factor 2 for the affine terms and z^(1/p).  A product without the third plane
+or without the three products of order 2^-16 is further off
+(emulated in numpy, p = 4, kappa 40: 4.6e-6 to 7.2e-6 against a limit of 2.0e-6).
 """
 import numpy as np
 import pytest
@@ -40,6 +46,14 @@ def _roots(env, mats, **params):
     return [host(x) for x in Xs], B.decode_root_info(info)
 
 
+def bound(kappa, p, n, info):
+    # the first update takes a largest eigenvalue of (p + 1) / 2 down to `low`
+    # in a product of matrices of norm (1 + 1/p)^p and (p + 1) / 2
+    low = ((p + 1) / (2 * p)) ** p * (p + 1) / 2
+    kappa = max(kappa, (1 + 1 / p) ** p * (p + 1) / 2 / low)
+    return 2 * (kappa / p + info["iters"]) * 2.0 ** -24 + n * info["resid"] / p
+
+
 SIZES = [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128]
 KAPPA = 40.0
 
@@ -53,10 +67,27 @@ def test_sizes_and_orders(env, p, scaling):
     xs, info = _roots(env, mats, p=p, scaling=scaling, precision=B.PRECISION_FP32)
     for a, x, i in zip(mats, xs, info):
         n = a.shape[0]
-        assert i["status"] in (B.ROOT_CONVERGED, B.ROOT_STAGNATED), (n, i)
+        assert i["status"] == B.ROOT_CONVERGED, (n, i)
         assert np.array_equal(x, x.T)
         err = rel(x, O.inv_root(a.astype(np.float64), p, 1e-6)[0])
-        assert err <= max(1, i["iters"]) * p * KAPPA * np.sqrt(n) * 2.0 ** -24, (n, err)
+        assert err <= bound(KAPPA, p, n, i), (n, err, i)
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("p", [6, 8])
+def test_rounding_does_not_accumulate_near_identity(env, n, p):
+    """Root mean square error over 24 well-conditioned matrices (kappa 9): the
+    roundings of M0 (amplified by kappa / p), of X in each iteration and of the
+    result, taken as independent and half a unit each.  Products of iterates
+    near I that lose their small terms add the same error to every eigenvalue
+    (5 to 7 units here)."""
+    say(f"small roots rms n={n} p={p}")
+    mats = [spd(n, 9.0, 1000 + k) for k in range(24)]
+    torch, B, dev, h = env
+    xs, info = _roots(env, mats, p=p, precision=B.PRECISION_FP32)
+    e = np.array([rel(x, O.inv_root(a.astype(np.float64), p, 1e-6)[0]) for a, x in zip(mats, xs)])
+    limit = 0.5 * (9.0 / p + np.sqrt(max(i["iters"] for i in info)) + 1) * 2.0 ** -24
+    assert np.sqrt((e ** 2).mean()) <= limit, (float(np.sqrt((e ** 2).mean())), limit)
 
 
 def test_relative_damping_asymmetric_input(env):
@@ -72,7 +103,7 @@ def test_relative_damping_asymmetric_input(env):
         lam = np.linalg.eigvalsh(s)[-1]
         assert abs(i["lambda_max"] / lam - 1) < 0.05
         w = O.inv_root(s, 4, i["eps_eff"])[0]
-        assert rel(x, w) <= i["iters"] * 4 * KAPPA * np.sqrt(len(a)) * 2.0 ** -24
+        assert rel(x, w) <= bound(KAPPA, 4, len(a), i), (len(a), rel(x, w), i)
 
 
 def test_outcomes_and_mixed_call(env):
@@ -99,7 +130,8 @@ def test_outcomes_and_mixed_call(env):
     assert ia[3]["status"] == B.ROOT_NOT_PD and ia[4]["status"] == B.ROOT_NOT_PD
     for k in (0, 1, 5, 6):
         a = small[k].astype(np.float64)
-        assert ia[k]["precision"] == 32 and rel(alone[k], O.inv_root(a, 4, 1e-6)[0]) <= ia[k]["iters"] * 4 * 30 * 11.4 * 2.0 ** -24
+        assert ia[k]["precision"] == 32
+        assert rel(alone[k], O.inv_root(a, 4, 1e-6)[0]) <= bound(30, 4, len(a), ia[k]), k
     assert rel(mixed[0], O.inv_root(big[0].astype(np.float64), 4, 1e-6)[0]) <= 1e-4
     # zero iterations: 1 x 1, p = 1, Frobenius scaling: z A = 1 exactly
     x, i = _roots(env, [np.array([[4.0]], np.float32)], p=1, eps=0.0, scaling=0, precision=B.PRECISION_FP32)
