@@ -1652,9 +1652,18 @@ shampoo_status inv_root_impl(Handle* h, const shampoo_root_job* jobs, int njobs,
       q.esc_n = esc_n;
       q.tol = prm->tol;
       q.eps = eps;
-      STATUS_TRY(launch(h, SHAMPOO_KCLASS_NEWTON_F32, s, [&] {
-        hipLaunchKernelGGL(newton_small_kernel, dim3(nsmall), dim3(kSmallThreads), 0, s, j32, njobs - nsmall, st, q);
-      }));
+      const int first = njobs - nsmall, nb = cdiv(jobs[first].n, 32);
+      auto run = [&](auto shape) {
+        constexpr int NB = decltype(shape)::value;
+        return launch(h, SHAMPOO_KCLASS_NEWTON_F32, s, [&] {
+          hipLaunchKernelGGL(newton_small_kernel<NB>, dim3(nsmall), dim3(SmallShape<NB>::threads), 0, s, j32, first, st,
+                             q);
+        });
+      };
+      STATUS_TRY(nb == 1   ? run(std::integral_constant<int, 1>{})
+                 : nb == 2 ? run(std::integral_constant<int, 2>{})
+                 : nb == 3 ? run(std::integral_constant<int, 3>{})
+                           : run(std::integral_constant<int, 4>{}));
     }
     if (cold && !all_small)
       STATUS_TRY(newton_phase<float>(h, j32, tl, njobs, st, dcount, up, full, flat, prog, p, prm->scaling, prm->tol,

@@ -31,14 +31,31 @@
 
 namespace shp {
 
-constexpr int kSmallMax = 128;       // largest n
+// Largest n, at any number of matrices.  Measured against grouped launches, us:
+// 128 x 128 1: 466 -> 210, 400: 808 -> 420, 4000: 7680 -> 4400; 96 x 96 4000:
+// 6630 -> 3070; 64 x 64 1: 445 -> 145, 10000: 10200 -> 2610; 8 x 8 1: 381 -> 149,
+// 10000: 3780 -> 955.
+constexpr int kSmallMax = 128;
 // E shrinks below anything an M in 32 bits could show: a residual of at most
 // this that was still above tol ends the iteration as the rounding floor.
 constexpr float kSmallFloor = 0x1p-20f;
-constexpr int kSmallThreads = 1024;  // 16 waves; a matrix of NB^2 < 16 blocks uses the first NB^2
-// planes of a 128-wide operand pair, ten 32 x 33 exchange blocks, reductions
 constexpr int kSmallExchange = 32 * 33;  // floats of one exchanged block (padded rows)
-constexpr int kSmallShm = 8 * 3 * 4096 + 10 * kSmallExchange * 4 + 64 * 8;
+
+// A launch for matrices of at most NB x NB blocks: one wave per block, the
+// planes of an operand pair, one exchange block per upper block, reductions.
+// Launches of small matrices so share a compute unit: with the shape of NB = 4
+// for all, a compute unit took one matrix at a time and 10000 roots of 8 x 8
+// 3980 us, of 64 x 64 6000 (grouped launches 3780 and 10200); now 955 and 2610.
+// Three waves per SIMD hold the iterates without spilling up to NB = 2 (two:
+// 1055 and 3280, four: 965 and 2520 with 72 registers spilled, and a single
+// root 4% slower).
+constexpr int kSmallWaves = 3;
+template <int NB>
+struct SmallShape {
+  static constexpr int threads = 64 * NB * NB;
+  static constexpr int planes = 2 * NB * 3 * NB * kBlockB;
+  static constexpr int shm = planes + NB * (NB + 1) / 2 * kSmallExchange * 4 + 16 * 8;
+};
 
 struct SmallRootArgs {
   int p, power, max_iters, eps_relative, esc_n;
@@ -451,14 +468,14 @@ struct SmallRoot {
   }
 };
 
-// One workgroup per job from `first` on (n <= 128, largest first); jobs that
+// One workgroup per job from `first` on (n <= 32 NB, largest first); jobs that
 // are not active (NOT_PD, sent to fp64 by the condition witness, kept from a warm
 // start) are left alone.  Waves past the matrix's blocks end at once (a
 // barrier counts the waves that are left).
-__global__ __launch_bounds__(kSmallThreads) void newton_small_kernel(const NewtonJob<float>* __restrict__ jobs,
-                                                                    int first,
-                                                                    RootState* __restrict__ st, SmallRootArgs q) {
-  __shared__ __attribute__((aligned(16))) char smem[kSmallShm];
+template <int NB>
+__global__ __launch_bounds__(SmallShape<NB>::threads, kSmallWaves) void newton_small_kernel(
+    const NewtonJob<float>* __restrict__ jobs, int first, RootState* __restrict__ st, SmallRootArgs q) {
+  __shared__ __attribute__((aligned(16))) char smem[SmallShape<NB>::shm];
   const int j = first + blockIdx.x;
   if (st[j].status != kActive) return;
   SmallRoot s;
@@ -470,8 +487,8 @@ __global__ __launch_bounds__(kSmallThreads) void newton_small_kernel(const Newto
   if (s.wave >= s.waves) return;
   s.lane = threadIdx.x & 63;
   s.smem = smem;
-  s.ex = reinterpret_cast<float*>(smem + 8 * 3 * 4096);
-  s.red = reinterpret_cast<double*>(s.ex + 10 * kSmallExchange);
+  s.ex = reinterpret_cast<float*>(smem + SmallShape<NB>::planes);
+  s.red = reinterpret_cast<double*>(s.ex + NB * (NB + 1) / 2 * kSmallExchange);
   s.place();
   s.run(jobs[j], st[j], q);
 }

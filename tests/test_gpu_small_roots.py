@@ -73,6 +73,22 @@ def test_sizes_and_orders(env, p, scaling):
         assert err <= bound(KAPPA, p, n, i), (n, err, i)
 
 
+@pytest.mark.parametrize("p", [4, 7])
+def test_launch_shapes_same_bits(env, p):
+    """A matrix alone (a launch shaped for its blocks) and beside larger ones."""
+    torch, B, dev, h = env
+    mats = [spd(n, KAPPA, 100 + n) for n in SIZES]
+    say(f"small roots launch shapes p={p}")
+    xs, info = _roots(env, mats, p=p)
+    for a, x, i in zip(mats, xs, info):
+        (y,), (k,) = _roots(env, [a], p=p)
+        assert np.array_equal(x, y) and i == k, a.shape
+    for k in (3, 6, 9):  # the largest of 32, 64 and 96 rows and those below it
+        ys, _ = _roots(env, mats[:k + 1][::-1] * 3, p=p)
+        for j, y in enumerate(ys):
+            assert np.array_equal(y, xs[k - j % (k + 1)]), (k, j)
+
+
 @pytest.mark.parametrize("n", [16, 32, 64])
 @pytest.mark.parametrize("p", [6, 8])
 def test_rounding_does_not_accumulate_near_identity(env, n, p):
