@@ -725,13 +725,13 @@ struct RootProduct<float, LA, LB, MODE> {
 template <int LA, int LB, int MODE>
 struct RootProduct<double, LA, LB, MODE> {
   typedef WaveAcc<double> Acc;
-  static constexpr int bytes = 16;
+  static constexpr int na = StageElems<double, LA>::value, nb = StageElems<double, LB>::value;
+  static constexpr int bytes = 2 * (na + nb) * 8;
   static __device__ __forceinline__ void run(Acc& acc, const Operand<double>& A, const Operand<double>& B, int m0,
-                                             int n0, int K, char*, bool diag) {
-    __shared__ __attribute__((aligned(16))) double a0[StageElems<double, LA>::value], a1[StageElems<double, LA>::value];
-    __shared__ __attribute__((aligned(16))) double b0[StageElems<double, LB>::value], b1[StageElems<double, LB>::value];
+                                             int n0, int K, char* smem, bool diag) {
+    double* a0 = reinterpret_cast<double*>(smem);
     acc.zero();
-    tile_mma<double, LA, LB>(acc, A, B, m0, n0, K, a0, a1, b0, b1, diag);
+    tile_mma<double, LA, LB>(acc, A, B, m0, n0, K, a0, a0 + na, a0 + 2 * na, a0 + 2 * na + nb, diag);
   }
 };
 

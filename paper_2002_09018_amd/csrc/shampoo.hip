@@ -347,10 +347,9 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
     }
   }
   auto k = gemm_grouped_kernel<SA, LA, SB, LB, LIM, SGG, SHORT>;
-  const int lds = 0;  // static LDS
   const int np = (int)probs.size();
   STATUS_TRY(launch(h, cls, s, [&] {
-    hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, s, (const GemmProblem*)d, np, total, map);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), 0, s, (const GemmProblem*)d, np, total, map);
   }));
   return SHAMPOO_OK;
 }
