@@ -8,7 +8,7 @@
 // with 255 idle.  Here the 16 blocks of a tile go to 16 waves on different
 // compute units, without LDS or barriers, and a step is 6 MFMAs and the
 // splitting of 16 values per lane.  Each block repeats that splitting, so the
-// form only pays while most of the chip would be idle (kDirectTiles).
+// form only pays while most of the chip would be idle (kDirectBlocks).
 //
 // The arithmetic of every output is that of split_mfma.hpp, operation for
 // operation (same MFMA, same order of products, same runs), so results do

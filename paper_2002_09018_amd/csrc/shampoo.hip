@@ -282,17 +282,31 @@ constexpr int kDiagLastMaxPerXcd = 128;
 // share the slabs of G they read in L2.
 constexpr int kDiagLastMinK = 2048;
 
-// Launches of at most this many 128 x 128 tiles take the one-wave-per-block
-// form (direct_mma.hpp; results are the same bits).  Measured, tiles per
-// launch: time with 128 x 128 workgroups -> direct.
-//   Statistics call (two launches): 1: 48 -> 25 us (128 x 128); 40: 88 -> 60
-//   us (512 x 512); 72: 166 -> 152 us (1024 x 1024); 80: 89 -> 98 us (512 x
-//   512); 96: 63 -> 71 us (256 x 256).
+// Launches of few tiles take the one-wave-per-block form (direct_mma.hpp;
+// results are the same bits).  A tile is 16 such blocks, a diagonal one of a
+// symmetric product 10, and the chip has 1024 SIMDs: GEMM launches take the
+// form up to kDirectBlocks blocks, just past one wave per SIMD, and kDirectTiles
+// tiles; bf16 x bf16, whose loads bound both forms, up to kDirectBlocksBf16
+// blocks where the contraction is beyond kDirectBf16K; root calls, whose products
+// follow each other, up to kDirectRootTiles tiles.  Measured with 128 x 128
+// workgroups -> direct, time by launch:
+//   Statistics (two launches): 1 tile, 48 -> 25 us (128 x 128); 40, 544 blocks,
+//   88 -> 60 us (512 x 512); 72, 1056 blocks, 166 -> 152 us (1024 x 1024); 80,
+//   1088 blocks, 89 -> 98 us (512 x 512); 100, 1000 blocks, 220 -> 238 us (128 x
+//   4096).  In bf16: 72, 720 blocks, 28 -> 23 us (128 x 128) but 98 -> 140 (128 x
+//   4096); 10, 136 blocks, 79 -> 73 us (512 x 4096); 30, 390 blocks, 69 -> 103 us
+//   (333 x 3000).
+//   Preconditioning, every size and both types, mean (and worst) ratio: up to 64
+//   tiles, 1024 blocks, 0.80 (1.17), with the fused graft 0.93 (1.17); 72 tiles
+//   1.10 (1.20) and 1.25 (1.35); 96 tiles 1.24 (1.80) and 1.20 (1.67).
 //   Root call (products of 1 or 2 times the tiles): 3: 489 -> 329 us (256 x
 //   256); 72: 1037 -> 860 us (1024 x 1024); 80: 682 -> 586 us, and 627 us with
 //   its two-product stages (160 tiles) direct as well (512 x 512); 96: 543 ->
 //   485 us (256 x 256).
 constexpr int kDirectTiles = 72;
+constexpr int kDirectBlocks = 1056;
+constexpr int kDirectBlocksBf16 = 160;
+constexpr int kDirectBf16K = 256;
 constexpr int kDirectRootTiles = 96;
 
 template <typename SA, int LA, typename SB, int LB, bool LIM = false, typename SGG = void, bool SHORT = false>
@@ -305,7 +319,7 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
     STATUS_TRY((run_gemm<SA, LA, SB, LB, false, SGG, true>(h, rest, s, cls)));
   }
   if (probs.empty()) return SHAMPOO_OK;
-  int total = 0, mixed = 0, sym = 1;
+  int total = 0, diags = 0, mixed = 0, sym = 1;
   for (const auto& p : probs) mixed |= p.M != probs[0].M || p.N != probs[0].N || p.K != probs[0].K;
   // Tiles with the longest contraction start first, so that a launch does
   // not end on a few of them (each problem's result does not depend on its
@@ -316,6 +330,7 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
     p.tiles_n = cdiv(p.N, kTile);
     p.tile_begin = total;
     total += p.sym ? p.tiles_n * (p.tiles_n + 1) / 2 : cdiv(p.M, kTile) * p.tiles_n;
+    if (p.sym) diags += p.tiles_n;
     sym &= p.sym;
   }
   // problems of different sizes: tiles dealt in chunks over the XCDs (grid
@@ -331,7 +346,10 @@ shampoo_status run_gemm(Handle* h, std::vector<GemmProblem>& probs, hipStream_t 
   const void* d = nullptr;
   STATUS_TRY(upload_table(h, probs.data(), probs.size() * sizeof(GemmProblem), s, &d));
   if constexpr (!LIM) {
-    if (total <= kDirectTiles) {
+    int kmax = 0;
+    for (const auto& p : probs) kmax = std::max(kmax, p.K);
+    const bool bf16_long = sizeof(SA) == 2 && sizeof(SB) == 2 && kmax > kDirectBf16K;
+    if (total <= kDirectTiles && 16 * total - 6 * diags <= (bf16_long ? kDirectBlocksBf16 : kDirectBlocks)) {
       const int np = (int)probs.size();
       return launch(h, cls, s, [&] {
         hipLaunchKernelGGL((gemm_direct_kernel<SHORT, SA, LA, SB, LB>), dim3(16 * total), dim3(64), 0, s,
