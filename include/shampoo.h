@@ -434,14 +434,14 @@ shampoo_status shampoo_embedding_graft(void* handle, const int32_t* rows, const 
  * (ms) and launch count of one class, and clears that class.
  */
 enum {
-  SHAMPOO_KCLASS_NEWTON_F32 = 0, /* grouped Newton products, fp32 MFMA */
-  SHAMPOO_KCLASS_NEWTON_F64 = 1, /* grouped Newton products, fp64 MFMA */
+  SHAMPOO_KCLASS_NEWTON_F32 = 0, /* grouped Newton products, fp32 */
+  SHAMPOO_KCLASS_NEWTON_F64 = 1, /* grouped Newton products, fp64 */
   SHAMPOO_KCLASS_STATS = 2,      /* grouped statistics SYRK */
   SHAMPOO_KCLASS_PRECOND = 3,    /* grouped preconditioning GEMMs */
   SHAMPOO_KCLASS_GRAFT = 4,      /* graft reduction and update passes */
   SHAMPOO_KCLASS_ROOT_AUX = 5,   /* root prologue/epilogue/state kernels */
   SHAMPOO_KCLASS_EMB = 6,        /* embedding row compaction (sort, runs, segment sums) */
-  SHAMPOO_KCLASS_NEWTON_WARM = 7, /* full products of warm-started roots (fp32 or fp64 MFMA) */
+  SHAMPOO_KCLASS_NEWTON_WARM = 7, /* full products of warm-started roots (fp32 or fp64) */
   SHAMPOO_KCLASS_COUNT = 8
 };
 shampoo_status shampoo_timing_enable(void* handle, int enable);

@@ -83,7 +83,8 @@ struct TableEntry {
 // Cached tables per handle, and the bytes of an entry's slot in the handle's
 // slabs (larger tables are allocated).  A step over one of a few gradient
 // buffers uses about six tables: 64 entries were replaced in turn by a
-// program cycling 16 buffers, a copy before every launch.
+// program cycling 16 buffers, a copy before every launch.  Beyond about 40
+// buffers in turn every table is copied again, as it was beyond 10.
 constexpr int kTableEntries = 256;
 constexpr size_t kTableSlot = 4096;
 
