@@ -3,9 +3,9 @@
 Workload (C2): 96 blocks, each with statistics L (1024 x 1024) built from 19
 earlier gradients and a current gradient G (1024 x 4096) ~ N(0, 1/4096); a
 step is one pass of the whole hot path over the 96 blocks:
-    L += G G^T                       (grouped fp32-MFMA SYRK)
+    L += G G^T                       (grouped SYRK, fp32 results)
     Lr = (L + 1e-6 I)^(-1/4)         (96 roots in one grouped coupled-Newton call)
-    P = Lr G                         (grouped fp32-MFMA GEMM; R side not tracked)
+    P = Lr G                         (grouped GEMM; R side not tracked)
     D += G o G, graft, W -= eta P    (two HBM passes)
 All inputs are resident in HBM before timing.  Before every step L is restored
 to its pristine value L_19 (a device copy inside the timed region, reported

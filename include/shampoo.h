@@ -67,10 +67,10 @@ enum {
 
 /* Arithmetic used for roots (shampoo_root_params.precision). */
 enum {
-  SHAMPOO_PRECISION_FP32 = 0, /* fp32 MFMA only */
-  SHAMPOO_PRECISION_AUTO = 1, /* fp32 MFMA; matrices that need more iterations than a matrix
+  SHAMPOO_PRECISION_FP32 = 0, /* fp32 only */
+  SHAMPOO_PRECISION_AUTO = 1, /* fp32; matrices that need more iterations than a matrix
                                  of condition kappa32 would (or that fail) are redone in fp64 */
-  SHAMPOO_PRECISION_FP64 = 2  /* fp64 MFMA only */
+  SHAMPOO_PRECISION_FP64 = 2  /* fp64 only */
 };
 
 /*

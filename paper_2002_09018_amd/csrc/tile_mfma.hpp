@@ -116,7 +116,7 @@ struct Operand {
   const S* ptr;
   int64_t ld;
   int rows, cols;
-  bool aligned;  // ptr and ld allow 16-byte vector loads
+  bool aligned;  // ptr and ld allow 16-byte vector loads (read by the fp64 staging)
 };
 
 // Per-thread staging registers for one operand stage (fp64).
